@@ -133,15 +133,31 @@ __device__ __forceinline__ float row_sum16_t(f4 v) {
 
 // ------------------------------------------------------------------------------- plan ----
 
+// How the persistent waves of k_herm_solve come by their chunks.  Atomics on one address are
+// performed one after the other, about 11.5 ns each on this part: with one counter the 9W
+// successful and W failing claims of a half-sweep took 0.47 ms at W = 4,096 (f = 16 and 40: all of
+// the time of a call on 50,000 or 1M ratings), and the waves' first claims alone 25-47 us.  So
+//   - a short sweep (at most kStaticEntries entry equivalents of cost per wave) claims nothing: wave
+//     w runs large chunk w and the eight small chunks W + 8w .. W + 8w + 7, an equal share of the
+//     cost;
+//   - a longer one, whose waves finish at different times, claims from kStripes counters on lines
+//     of their own: stripe s holds chunks s, s + kStripes, ... in order, for the waves of blocks
+//     b with b / 8 = s (mod kStripes), which lie on all XCDs (block b runs on XCD b mod 8).  A
+//     stripe's 128 or more waves even it out among themselves, so none goes on to another stripe
+//     (looking at the other counters at the end made the kernel twice as long).
+constexpr int kStripes = 16;                    // a power of two
+constexpr int kStripeWords = 64;                // 256 bytes apart
+constexpr int64_t kStaticEntries = 2048;
+
 // Cost prefix P(u) = c_nnz rowptr[u] + c_row u, T = P(m).  C chunks: W large ones cover
 // T1 = T - T2 and C - W small ones the tail T2 = floor(T / kTailDiv) (T2 = 0 when C = W);
 // boundary b sits at s_b = floor(T1 b / W) for b <= W, T1 + floor(T2 (b - W) / (C - W)) beyond.
-// Thread 0 also resets the chunk counter the persistent waves claim chunks from.
+// The first threads also reset the counters the persistent waves claim chunks from.
 __global__ void k_plan(const int64_t* __restrict__ rowptr, int64_t m, int W, int C, int64_t c_nnz,
                        int64_t c_row, int64_t q, int64_t* __restrict__ bounds,
                        unsigned* __restrict__ chunk_ctr) {
     const int b = blockIdx.x * blockDim.x + threadIdx.x;
-    if (b == 0 && chunk_ctr) *chunk_ctr = 0u;
+    if (b < kStripes && chunk_ctr) chunk_ctr[b * kStripeWords] = 0u;
     if (b > C) return;
     const int64_t T = c_nnz * rowptr[m] + c_row * m;
     const int64_t T2 = C > W ? T / kTailDiv : 0, T1 = T - T2;
@@ -1105,7 +1121,7 @@ __device__ __forceinline__ void write_zero_row(float* __restrict__ xrow, int f, 
 
 // ------------------------------------------------------------------------ kernels --------
 
-// Persistent waves claim chunks in order from a counter; chunk c covers the entries from
+// Persistent waves claim chunks in order (see kStripes); chunk c covers the entries from
 // bounds[c] to bounds[c+1].  Whole rows are solved here; the piece of a row cut at the start of
 // the chunk goes to slot 2c, the piece cut at its end to slot 2c+1, so what is stored where does
 // not depend on which wave ran the chunk.  Rows are software-pipelined: the next piece's index
@@ -1116,6 +1132,23 @@ struct Piece {
     bool whole;            // the chunk holds the whole row
 };
 
+// Bit j set: chunk first + j (j < kSmallPerWave) is not empty.
+__device__ __forceinline__ unsigned nonempty_chunks(const int64_t* __restrict__ bounds, int first,
+                                                    int lane) {
+    const int j = lane < kSmallPerWave ? lane : kSmallPerWave - 1;
+    const int64_t* b = bounds + 2 * (int64_t)(first + j);
+    const bool some = b[0] != b[2] || b[1] != b[3];
+    return (unsigned)__ballot(some && lane < kSmallPerWave);
+}
+
+// The next chunk of a stripe, from its counter; C or more when it is used up.  Every lane takes part
+// in the claim (lane 0 adds one, the others zero).
+__device__ __forceinline__ int claim_chunk(unsigned* __restrict__ ctr, int stripes, int stripe,
+                                           int lane) {
+    const unsigned got = atomicAdd(ctr + stripe * kStripeWords, lane == 0 ? 1u : 0u);
+    return __builtin_amdgcn_readfirstlane((int)got) * stripes + stripe;
+}
+
 template <int NB, int BUF, int P, bool PARTS>
 __global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(NB <= 8 ? 2 : 1)))
 void k_herm_solve(
@@ -1124,8 +1157,8 @@ void k_herm_solve(
     int f, float lambda, int C, const int64_t* __restrict__ bounds, float* __restrict__ x_out,
     float* __restrict__ slots, float* __restrict__ wave_slots, int part_mask, int64_t c_row,
     unsigned long long* __restrict__ nonspd, unsigned* __restrict__ chunk_ctr) {
-    // Both instantiations (with and without parts) are launched; the one that does not match
-    // this call returns at once.  A piece lies within a chunk and within a row: a chunk holds at
+    // Where a piece may be longer than a part, both instantiations (with and without parts) are
+    // launched, and the one that does not match this call returns at once.  A piece lies within a chunk and within a row: a chunk holds at
     // most ceil(T1 / W) cost units (c_nnz per entry) plus the snapping of its two cut offsets,
     // and a row at most n entries (its columns are distinct).
     {
@@ -1145,15 +1178,34 @@ void k_herm_solve(
     }
     const Gather<NB, BUF, P> gat(theta, n, f, lane & 15, stage);
     float* __restrict__ wslot = wave_slots + (size_t)blockIdx.x * slot_floats(NB);
-    // No lane-0-only region in the claim loop: every lane takes part in the claim (lane 0 adds
-    // one, the others zero), and the wave's count of non-SPD rows stays in a register until the
+    // No lane-0-only region in the claim loop: every lane takes part in a claim, and the wave's
+    // count of non-SPD rows stays in a register until the
     // loop has ended (a lane-0 region at each end of a loop body can be joined across the back
     // edge, leaving lanes 1..63 in a loop of their own).
     unsigned bad = 0;
+    const int W = (int)gridDim.x, self = (int)blockIdx.x;
+    const bool fixed = kCostPerEntry * rowptr[m] + c_row * m <=
+                       kStaticEntries * kCostPerEntry * (int64_t)W;
+    bool first = true;
+    const int stripes = W >= 8 * kStripes ? kStripes : 1;   // each with waves of its own
+    const int stripe = (self >> 3) & (stripes - 1);
+    unsigned small = 0;                                     // the wave's small chunks to run
     for (;;) {
-        const unsigned got = atomicAdd(chunk_ctr, lane == 0 ? 1u : 0u);
-        const int c = __builtin_amdgcn_readfirstlane((int)got);
-        if (c >= C) break;
+        int c;
+        if (fixed) {
+            if (first) {
+                c = self;
+                if (C > W) small = nonempty_chunks(bounds, W + kSmallPerWave * self, lane);
+            } else {
+                if (small == 0) break;
+                c = W + kSmallPerWave * self + __builtin_ctz(small);
+                small &= small - 1;
+            }
+            first = false;
+        } else {
+            c = claim_chunk(chunk_ctr, stripes, stripe, lane);
+            if (c >= C) break;
+        }
         const int64_t u0 = bounds[2 * c], k0 = bounds[2 * c + 1];
         const int64_t u1 = bounds[2 * c + 2], k1 = bounds[2 * c + 3];
         // the first piece with entries at or after row u; empty rows on the way get x_u = 0
@@ -1234,6 +1286,11 @@ void k_herm_solve(
 // first piece and the group sums, in order, and solves.  The order is fixed, so the result does
 // not depend on timing.
 constexpr int kPieceGroup = 16;
+// Blocks of the reduce kernels.  One per boundary cost 9 us a kernel where no row is cut (tiny,
+// C = 36,864); 2,048 (all resident at f = 100) leave each wave up to nine cut rows one after the
+// other: 133 us against 95 for k_reduce_solve on the movie user side, and 296 us against 264 for a
+// whole iteration on 1M ratings at f = 40.  With 8,192 the tiny call takes 23.3 us, with 2,048 21.2.
+constexpr int kReduceWaves = 8192;
 
 __device__ __forceinline__ bool cuts_row(const int64_t* __restrict__ rowptr, int64_t m,
                                          const int64_t* __restrict__ bounds, int b) {
@@ -1296,40 +1353,57 @@ __device__ __forceinline__ void add_pieces(f4 (&acc)[ntiles(NB)], const int64_t*
     }
 }
 
-// Pass 1: one wave per internal boundary (the loop also serves smaller grids); group leaders of
-// long cut rows sum their group.
+// The internal boundaries 1 .. C - 1 are dealt to the waves of the grid in turn (wave j: 1 + j,
+// 1 + j + grid, ...).  A wave looks at 64 of its boundaries at once, a lane each, and takes up those
+// that cut a row one after the other.
+template <class Pick, class Take>
+__device__ __forceinline__ void for_boundaries(int C, int lane, Pick&& pick, Take&& take) {
+    const int grid = (int)gridDim.x;
+    for (int64_t b0 = 1 + (int64_t)blockIdx.x; b0 < C; b0 += (int64_t)grid * kWave) {
+        const int64_t b = b0 + (int64_t)lane * grid;
+        uint64_t todo = __ballot(b < C && pick((int)b));
+        while (todo) {
+            const int l = __builtin_ctzll(todo);
+            todo &= todo - 1;
+            take((int)(b0 + (int64_t)l * grid));
+        }
+    }
+}
+
+// Pass 1: group leaders of long cut rows sum their group.  A boundary's row has more than
+// kPieceGroup boundaries only if some kPieceGroup - 1 away or nearer lies in it too.
 template <int NB>
 __global__ __launch_bounds__(kWave) void k_reduce_groups(
     const int64_t* __restrict__ rowptr, int64_t m, int C, const int64_t* __restrict__ bounds,
     float* __restrict__ slots) {
     const int lane = threadIdx.x;
-    for (int b = blockIdx.x + 1; b < C; b += gridDim.x) {
-        if (!cuts_row(rowptr, m, bounds, b)) continue;
+    const auto pick = [&](int b) {
+        if (!cuts_row(rowptr, m, bounds, b)) return false;
+        const int64_t u = bounds[2 * b];
+        return (b > 1 && bounds[2 * (b - 1)] == u) || (b + 1 < C && bounds[2 * (b + 1)] == u);
+    };
+    for_boundaries(C, lane, pick, [&](int b) {
         const int64_t u = bounds[2 * b];
         int b_first, b_last;
         cut_range(rowptr, m, bounds, C, b, u, b_first, b_last);
-        if (b_last - b_first + 1 <= kPieceGroup || (b - b_first) % kPieceGroup != 0) continue;
+        if (b_last - b_first + 1 <= kPieceGroup || (b - b_first) % kPieceGroup != 0) return;
         f4 acc[ntiles(NB)];
 #pragma unroll
         for (int t = 0; t < ntiles(NB); ++t) acc[t] = f4{0.f, 0.f, 0.f, 0.f};
         const int to = b + kPieceGroup - 1 < b_last ? b + kPieceGroup - 1 : b_last;
         add_pieces<NB>(acc, bounds, slots, b, to, b_last, rowptr[u + 1] - rowptr[u], lane);
         store_slot<NB>(acc, slots + (size_t)(2 * b) * slot_floats(NB), lane);
-    }
+    });
 }
 
-// Pass 2: one wave per internal boundary (the loop also serves smaller grids); the first
-// boundary that cuts a row sums its pieces (or its group sums) and solves it.
+// Pass 2: the first boundary that cuts a row sums its pieces (or its group sums) and solves it.
 template <int NB>
 __device__ __forceinline__ void reduce_row(const int64_t* __restrict__ rowptr, int64_t m, int C,
                                            int f, float lambda, const int64_t* __restrict__ bounds,
                                            float* __restrict__ x_out,
                                            const float* __restrict__ slots, unsigned& bad,
                                            SolveLds<NB>& lds, int b, int lane) {
-    if (!cuts_row(rowptr, m, bounds, b)) return;
     const int64_t u = bounds[2 * b];
-    if (b > 1 && cuts_row(rowptr, m, bounds, b - 1) && bounds[2 * (b - 1)] == u)
-        return;   // not the first cut
     int b_first, b_last;
     cut_range(rowptr, m, bounds, C, b, u, b_first, b_last);
     f4 acc[ntiles(NB)];
@@ -1358,8 +1432,14 @@ __global__ __launch_bounds__(kWave) void k_reduce_solve(
     __shared__ __attribute__((aligned(16))) SolveLds<NB> lds;
     const int lane = threadIdx.x;
     unsigned bad = 0;   // non-SPD rows of this wave, added once after the loop
-    for (int b = blockIdx.x + 1; b < C; b += gridDim.x)
+    const auto first_cut = [&](int b) {
+        if (!cuts_row(rowptr, m, bounds, b)) return false;
+        return !(b > 1 && bounds[2 * (b - 1)] == bounds[2 * b] &&
+                 cuts_row(rowptr, m, bounds, b - 1));
+    };
+    for_boundaries(C, lane, first_cut, [&](int b) {
         reduce_row<NB>(rowptr, m, C, f, lambda, bounds, x_out, slots, bad, lds, b, lane);
+    });
     bad = __builtin_amdgcn_readfirstlane(bad);
     if (bad) atomicAdd(nonspd, lane == 0 ? (unsigned long long)bad : 0ull);
 }
@@ -1396,8 +1476,10 @@ struct RmseBody {
 };
 
 // RMSE partials: the entries are cut into C equal chunks, chunk w = [nnz w / C, nnz (w+1) / C);
-// persistent waves claim chunks in order from a counter and walk each row piece by row piece
-// through the gather pipeline (the next piece's index batches load during the current piece;
+// a grid of one wave per chunk takes chunk w in block w; a narrower one claims chunks in order from
+// a counter (about 11.5 ns per claim on its one address: the 8,192 + 8,192 claims of a full-width
+// grid took 0.19 ms, all of the time of a call on 1M ratings).  Each chunk is walked row piece by
+// row piece through the gather pipeline (the next piece's index batches load during the current piece;
 // x_u is loaded once per piece).  Chunk w's fp64 sum goes to partial[w], so the result does not
 // depend on how many waves run or which wave took which chunk: the kernel may run at any width,
 // e.g. one wave per SIMD beside a half-sweep.  NB = f / 16 + 1 (the gather's block count).
@@ -1415,9 +1497,15 @@ __global__ __launch_bounds__(kWave) void k_rmse_rows(
     // the others zero) and every lane stores the wave's sum.  (Two lane-0 regions at the ends of
     // the loop body were joined across the back edge by the compiler, leaving lanes 1..63 in a
     // loop of their own that read a stale chunk number.)
-    for (;;) {
-        const unsigned got = atomicAdd(claim, lane == 0 ? 1u : 0u);
-        const int w = __builtin_amdgcn_readfirstlane((int)got);
+    const bool claims = (int)gridDim.x < C;
+    for (int turn = 0;; ++turn) {
+        int w;
+        if (claims) {
+            const unsigned got = atomicAdd(claim, lane == 0 ? 1u : 0u);
+            w = __builtin_amdgcn_readfirstlane((int)got);
+        } else {
+            w = turn == 0 ? (int)blockIdx.x : C;
+        }
         if (w >= C) break;
         const int64_t kb = nnz / C * w + (nnz % C) * w / C;
         const int64_t ke = nnz / C * (w + 1) + (nnz % C) * (w + 1) / C;
@@ -1467,17 +1555,27 @@ __global__ __launch_bounds__(kWave) void k_rmse_rows(
     }
 }
 
-__global__ __launch_bounds__(kWave) void k_rmse_final(const int64_t* __restrict__ rowptr,
-                                                      int64_t m, int W,
-                                                      const double* __restrict__ partial,
-                                                      double* __restrict__ out) {
-    const int lane = threadIdx.x;
+// The partials' sum in a fixed order: thread t adds partials t, t + 1024, ..., then a butterfly
+// per wave and the waves in order.  (One wave with 128 loads, each waited for, took 33-42 us.)
+constexpr int kFinalThreads = 1024;
+
+__global__ __launch_bounds__(kFinalThreads) void k_rmse_final(const int64_t* __restrict__ rowptr,
+                                                              int64_t m, int W,
+                                                              const double* __restrict__ partial,
+                                                              double* __restrict__ out) {
+    __shared__ double sums[kFinalThreads / kWave];
+    const int t = threadIdx.x;
     double s = 0.0;
-    for (int i = lane; i < W; i += kWave) s += partial[i];
+#pragma unroll 8
+    for (int i = t; i < W; i += kFinalThreads) s += partial[i];
     for (int o = 32; o >= 1; o >>= 1) s += __shfl_xor(s, o);
-    if (lane == 0) {
+    if ((t & (kWave - 1)) == 0) sums[t / kWave] = s;
+    __syncthreads();
+    if (t == 0) {
+        double all = 0.0;
+        for (int i = 0; i < kFinalThreads / kWave; ++i) all += sums[i];
         const int64_t nnz = rowptr[m];
-        out[0] = nnz > 0 ? sqrt(s / (double)nnz) : 0.0;
+        out[0] = nnz > 0 ? sqrt(all / (double)nnz) : 0.0;
     }
 }
 
@@ -1755,7 +1853,8 @@ Layout make_layout(const int* waves, int nb_max, int cus) {
     }
     Layout L;
     size_t off = 0;
-    L.status = off; off = align256(off + 256);   // non-SPD counter at 0, chunk counters at 64, 128
+    // non-SPD counter at 0, RMSE chunk counter at 128, the half-sweep's chunk counters from 256 on
+    L.status = off; off = align256(off + 256 + sizeof(unsigned) * kStripes * kStripeWords);
     L.bounds = off; off = align256(off + sizeof(int64_t) * 2 * (size_t)(c_cap + 1));
     L.rmse = off;   off = align256(off + sizeof(double) * (size_t)cus * kRmseWavesPerCU);
     L.slots = off;  off = align256(off + slot_bytes);
@@ -1805,7 +1904,8 @@ int occupancy_waves(int cus, int* waves) {
 
 // Launch the RMSE partials kernel over C = cus * kRmseWavesPerCU chunks (the partials buffer
 // holds that many) with as many resident waves as fit, at most `cap_per_cu` per CU if that is
-// positive; the claim counter is reset first, on the same stream.
+// positive.  A grid of fewer waves than chunks claims them: its counter is reset first, on the
+// same stream.
 template <int NB, bool BUF>
 hipError_t rmse_rows_launch(int cus, int cap_per_cu, hipStream_t st, const int64_t* rowptr,
                             const int32_t* colidx, const float* vals, int64_t m, int64_t n,
@@ -1817,7 +1917,8 @@ hipError_t rmse_rows_launch(int cus, int cap_per_cu, hipStream_t st, const int64
     if (e != hipSuccess) return e;
     b = b < 1 ? 1 : (b > kRmseWavesPerCU ? kRmseWavesPerCU : b);
     if (cap_per_cu > 0 && b > cap_per_cu) b = cap_per_cu;
-    hipLaunchKernelGGL(k_reset_counter, dim3(1), dim3(1), 0, st, (unsigned long long*)claim);
+    if (cus * b < C)
+        hipLaunchKernelGGL(k_reset_counter, dim3(1), dim3(1), 0, st, (unsigned long long*)claim);
     hipLaunchKernelGGL((k_rmse_rows<NB, BUF>), dim3(cus * b), dim3(kWave), 0, st, rowptr,
                        colidx, vals, m, n, f, x, theta, C, part, claim);
     return hipGetLastError();
@@ -1983,14 +2084,16 @@ struct HermArgs {
     unsigned* chunk_ctr;
 };
 
-// Both instantiations; the kernels pick the one that runs from rowptr[m] on the device (no
-// host synchronisation), the other returns at once.
+// A row has at most n entries (its columns are distinct), so with n no longer than a part no piece
+// is.  Beyond that both instantiations are launched; the kernels pick the one that runs from
+// rowptr[m] on the device (no host synchronisation), the other returns at once (about 5 us).
 template <int NB, int BUF, int P>
 void launch_herm(int W, hipStream_t st, const HermArgs& a) {
     hipLaunchKernelGGL((k_herm_solve<NB, BUF, P, false>), dim3(W), dim3(kWave), 0, st,
                        a.rowptr, a.colidx, a.vals, a.theta, a.m, a.n, a.f, a.lambda, a.C,
                        a.bounds, a.x, a.slots, a.wslots, a.part_mask, a.c_row, a.nonspd,
                        a.chunk_ctr);
+    if (a.n <= (int64_t)kEntriesPerGroup * (a.part_mask + 1)) return;
     hipLaunchKernelGGL((k_herm_solve<NB, BUF, P, true>), dim3(W), dim3(kWave), 0, st,
                        a.rowptr, a.colidx, a.vals, a.theta, a.m, a.n, a.f, a.lambda, a.C,
                        a.bounds, a.x, a.slots, a.wslots, a.part_mask, a.c_row, a.nonspd,
@@ -2006,7 +2109,7 @@ void launch_sweep(als_ctx* ctx, const int64_t* rowptr, const int32_t* colidx, co
     float* wslots = (float*)(ctx->ws + ctx->lay.wave_slots);
     const int part_mask = ctx->part_groups - 1;
     auto* nonspd = (unsigned long long*)(ctx->ws + ctx->lay.status);
-    auto* chunk_ctr = (unsigned*)(ctx->ws + ctx->lay.status + 64);
+    auto* chunk_ctr = (unsigned*)(ctx->ws + ctx->lay.status + 256);
     const int C = chunks_of(W);
     hipEvent_t* ev = nullptr;
     if (ctx->prof_ev && ctx->prof_count < ctx->prof_cap) ev = ctx->prof_ev + 4 * ctx->prof_count++;
@@ -2043,10 +2146,10 @@ void launch_sweep(als_ctx* ctx, const int64_t* rowptr, const int32_t* colidx, co
     }
     if (ev) (void)hipEventRecord(ev[2], st);
     if (C > 1) {
-        // one wave per boundary: the rows' solves run side by side
-        hipLaunchKernelGGL(k_reduce_groups<NB>, dim3(C - 1), dim3(kWave), 0, st, rowptr, m, C,
+        const int grid = C - 1 < kReduceWaves ? C - 1 : kReduceWaves;
+        hipLaunchKernelGGL(k_reduce_groups<NB>, dim3(grid), dim3(kWave), 0, st, rowptr, m, C,
                            bounds, slots);
-        hipLaunchKernelGGL(k_reduce_solve<NB>, dim3(C - 1), dim3(kWave), 0, st, rowptr, m, C, f,
+        hipLaunchKernelGGL(k_reduce_solve<NB>, dim3(grid), dim3(kWave), 0, st, rowptr, m, C, f,
                            lambda, bounds, x, slots, nonspd);
     }
     if (ev) (void)hipEventRecord(ev[3], st);
@@ -2179,7 +2282,7 @@ hipError_t rmse_launch(int cus, int cap_per_cu, bool force_global, hipStream_t s
         }
         if (le != hipSuccess) return le;
     }
-    hipLaunchKernelGGL(k_rmse_final, dim3(1), dim3(kWave), 0, st, rowptr, m, m > 0 ? C : 0, part,
+    hipLaunchKernelGGL(k_rmse_final, dim3(1), dim3(kFinalThreads), 0, st, rowptr, m, m > 0 ? C : 0, part,
                        rmse_out);
     return hipGetLastError();
 }
