@@ -71,11 +71,11 @@ size_t als_workspace_bytes(int device, int32_t f_max);
    (for tests and ablation; results agree within the parity tolerance):
      ALS_GATHER=global      gather theta/x with 64-bit global loads at every size (otherwise
                             bounded buffer loads whenever the factor is below 2 GiB);
-     ALS_LAST_BLOCK=tiles   accumulate the last block column with 16x16x4 tiles even when its
-                            quad form applies (f = 0 or 4 mod 16).
+     ALS_LAST_BLOCK=tiles   accumulate the last block column as ordinary tiles even when a shorter
+                            form of it applies (f = 0 to 4 mod 16).
    A third sets the part length of long pieces (tests; the default is 65,536 entries):
-     ALS_PART_ENTRIES=k     a row piece longer than k entries (rounded down to 16 times a power
-                            of two) is accumulated in parts of that length, whose sums are added
+     ALS_PART_ENTRIES=k     a row piece longer than k entries (rounded down to 32 times a power
+                            of two, at least 32) is accumulated in parts of that length, whose sums are added
                             in order in a per-wave slot of the workspace (a two-level sum: no
                             fp32 running sum spans more than one part). */
 int als_init(als_ctx** ctx, int device, void* workspace, size_t workspace_bytes, int32_t f_max);
@@ -171,12 +171,13 @@ int als_plan(als_ctx* ctx, const int64_t* rowptr, int64_t m, int32_t f, int64_t*
  * Test and debug support: the gather stage of the half-sweep (Algorithm 1's read of the theta_v
  * of a row's rated columns) for row u, made visible.  The same gather form, index pipeline and
  * operand layout as als_half_sweep with this context and f run over row u, and instead of the
- * matrix products they write what each entry's operands hold.  With NB = f / 16 + 1, entry k
+ * matrix products they write the values that each entry's operands are made from.  With NB = f / 16 + 1, entry k
  * of the row (k < n_u) gets a record of 16 (NB + 3) floats at out + k 16 (NB + 3):
  *   [16 I + c]        block I of the MFMA operand, lane c: theta_v[16 I + c] for 16 I + c < f,
  *                     the rating r at 16 I + c == f, 0 beyond (I < NB);
- *   [16 (NB + p) + c] the quad-form operand w[p], when the last block column runs in quad form
- *                     (p < P): theta_v[16 (NB - 1) + 4 p + (c & 3)] for the theta quads, and for
+ *   [16 (NB + p) + c] for f = 0 or 4 mod 16, unless the last block column runs as ordinary tiles,
+ *                     the last block by quads of columns (p < P = (f mod 16) / 4 + 1):
+ *                     theta_v[16 (NB - 1) + 4 p + (c & 3)] for the theta quads, and for
  *                     the rating quad r at (c & 3) == 0, else 0 (untouched otherwise);
  *   [16 (NB + 2) + c] the rating r (every c).
  * Records past capacity (in floats) are not written.  Bit-exact against theta and vals.

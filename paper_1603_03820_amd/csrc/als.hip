@@ -8,16 +8,17 @@
 //   k_plan          integer partition of the rows (and of long rows' entries) into chunks of a
 //                   cost axis: W large chunks, then 8W small ones (see als_plan in als.h); no
 //                   host synchronisation needed.
-//   k_herm_solve    persistent waves claim chunks in order and walk their row pieces; gather
-//                   theta_v for four entries at a time straight into MFMA operand registers
-//                   (lane = 16*k + column, so each group of 16 lanes reads 64 contiguous bytes of
-//                   one theta_v), with the rating appended as column f, and accumulate the upper
-//                   block-triangle of the augmented Gram matrix [A b; b^T c] with
-//                   v_mfma_f32_16x16x4_f32 (the mostly-padding last block column with 4x4x1
-//                   16-block MFMAs when it fits whole quads).  Rows that end in the chunk are
-//                   regularised and solved in registers by a blocked Cholesky: per 16-column
-//                   block, the 16 x 16 diagonal tile is factored and inverted with lane
-//                   broadcasts, and the panel and trailing updates are again 16x16x4 MFMAs; the
+//   k_herm_solve    persistent waves take chunks in order and walk their row pieces; gather theta_v
+//                   for 32 entries at a time straight into MFMA operand layout (lane = 16*k +
+//                   column, so each group of 16 lanes reads 64 contiguous bytes of one theta_v),
+//                   with the rating appended as column f, split every value into three bf16 parts
+//                   that add up to it exactly, and accumulate the upper block-triangle of the
+//                   augmented Gram matrix [A b; b^T c] in fp32 with six
+//                   v_mfma_f32_16x16x32_bf16 per tile (three for the mostly-padding last block
+//                   column, an FMA per value when it holds the rating alone).  Rows that end in
+//                   the chunk are regularised and solved in registers by a blocked Cholesky: per
+//                   16-column block, the 16 x 16 diagonal tile is factored and inverted with lane
+//                   broadcasts, and the panel and trailing updates are 16x16x4 fp32 MFMAs; the
 //                   forward substitution rides along as the augmented column; the back
 //                   substitution is a short blocked pass.
 //   k_reduce_*      rows cut by chunk boundaries: sum the chunks' partial accumulators in chunk
@@ -38,6 +39,7 @@
 #include <cstring>
 #include <mutex>
 #include <new>
+#include <type_traits>
 
 #include "als.h"
 
@@ -57,9 +59,6 @@ constexpr int kRmseWavesPerCU = 32;                // RMSE: up to 8 waves per SI
 constexpr int kTransposeWavesPerCU = 8;            // CSR -> CSC: row blocks per CU (at most)
 
 constexpr int ntiles(int nb) { return nb * (nb + 1) / 2; }
-// the quad form with a theta quad (f = 16 (NB - 1) + 4) exists for NB whose f is in range
-template <int NB>
-constexpr bool kQuad2 = 16 * (NB - 1) + 4 <= ALS_F_MAX;
 // upper block-triangle, row-major: tile (I, J) with I <= J
 constexpr int tu(int nb, int I, int J) { return I * nb - I * (I - 1) / 2 + (J - I); }
 // floats per partial-accumulator slot: tiles, 4 per lane
@@ -189,7 +188,7 @@ __global__ void k_plan(const int64_t* __restrict__ rowptr, int64_t m, int W, int
 
 // --------------------------------------------------------------------- Gram + RHS --------
 
-// Gather pipeline: the gathers of step s + kDepth are issued before step s runs, so every gather
+// Gather pipeline of the RMSE: the gathers of step s + kDepth are issued before step s runs, so every gather
 // has kDepth steps of matrix work of this wave to hide behind.  Steps run in unrolled groups of
 // kGroup = kDepth + 1 with as many operand buffers; at sub-step J the step kDepth ahead goes into
 // the buffer whose step ran at sub-step J - 1, so the buffers rotate by renaming, never by copying
@@ -207,93 +206,23 @@ constexpr int kRing = 2 * kBatch;
 static_assert(kBatchGroups * kGroup * 4 == kBatch && kBatchGroups >= 2 && 2 * kDepth <= 11,
               "pipeline depth must divide the batch and stay within one group of lookahead");
 
-// The last block column NB-1 holds f - 16 (NB-1) theta columns and the rating, the rest of it
-// padding.  In the quad form (P > 0: the theta columns fill P-1 whole column quads and the
-// rating is column 4 (P-1) of the block) the 16x16 tiles cover only the block columns J < NB-1.
-// The theta columns of the last block are accumulated by v_mfma_f32_4x4x1_16b_f32 (16 blocks of
-// 4x4, lane 4b + i of the A operand holds row i of block b, so block b = 4e + qq is entry slot e,
-// row quad qq of an operand block exactly as gathered): q[I][p], lane 4b + j, register i holds
-// the slot-e part of M[16 I + 4 qq + i][16 (NB-1) + 4 p + j], with the second operand w[p]
-// holding column 4p + j of the entry's last block in every quad.  The rating column needs one
-// value per row, so it is a plain FMA per lane: b[I] at lane (e, c) holds the slot-e part of
-// M[16 I + c][f] (the lane's own operand times its slot's rating).
-template <int NB, int P>
-struct QuadAcc {
-    f4 q[NB][P > 1 ? P - 1 : 1];   // used for P > 1
-    float b[NB];
-};
-template <int NB>
-struct QuadAcc<NB, 0> {};
-
-template <int NB, int P>
-__device__ __forceinline__ void mfma_step(const float (&v)[NB], const float (&w)[P > 0 ? P : 1],
-                                          float r, f4 (&acc)[ntiles(NB)], QuadAcc<NB, P>& qa) {
-    constexpr int JT = P > 0 ? NB - 1 : NB;   // block columns covered by 16x16 tiles
-#pragma unroll
-    for (int I = 0; I < JT; ++I)
-#pragma unroll
-        for (int J = I; J < JT; ++J)
-            acc[tu(NB, I, J)] =
-                __builtin_amdgcn_mfma_f32_16x16x4f32(v[I], v[J], acc[tu(NB, I, J)], 0, 0, 0);
-    if constexpr (P > 0) {
-#pragma unroll
-        for (int I = 0; I < NB; ++I)
-#pragma unroll
-            for (int p = 0; p + 1 < P; ++p)
-                qa.q[I][p] = __builtin_amdgcn_mfma_f32_4x4x1f32(v[I], w[p], qa.q[I][p], 0, 0, 0);
-#pragma unroll
-        for (int I = 0; I < NB; ++I) qa.b[I] = __builtin_fmaf(v[I], r, qa.b[I]);
-    }
+// The last block column NB-1 holds q = f - 16 (NB-1) + 1 real columns, the last theta columns and
+// the rating; the rest of it is padding.  Its form (LAST):
+//   kLastRating  q = 1, the rating alone (f a multiple of 16): no operand block; the rating column is
+//                one fp32 FMA per gathered value;
+//   kLastPacked  q <= 5: lane c holds column c mod q, the real columns three times over, for the
+//                three parts of the split below;
+//   kLastTiles   otherwise: lane c holds column c, an ordinary block.
+constexpr int kLastTiles = 0, kLastPacked = 1, kLastRating = 2, kLastForms = 3;
+constexpr int kPackedColumns = 5;
+constexpr int last_form(int f) {
+    return f % 16 == 0 ? kLastRating : (f % 16 + 1 <= kPackedColumns ? kLastPacked : kLastTiles);
 }
-
-// The quad accumulators into standard tiles acc[tu(NB, I, NB-1)]: the tile's lane (g, c),
-// register r needs M[16 I + 4 g + r][16 (NB-1) + c] = the sum over entry slots e = 0..3, in that
-// order, of q[I][c / 4] at lane 16 e + 4 g + (c & 3), register r, for the theta columns, and of
-// b[I] at lane 16 e + 4 g + r for the rating column; columns past it stay 0.  One LDS exchange
-// for both.  scratch: (P - 1) NB 64 vectors then NB 64 floats, 16-byte aligned.
-template <int NB, int P>
-constexpr int quad_scratch_bytes() {
-    return (P - 1) * NB * kWave * 16 + NB * kWave * 4;
-}
-template <int NB, int P>
-__device__ __forceinline__ void quad_to_tiles(const QuadAcc<NB, P>& qa, f4 (&acc)[ntiles(NB)],
-                                              void* scratch, int lane) {
-    const int g = lane >> 4, c = lane & 15;
-    f4* sq = reinterpret_cast<f4*>(scratch);
-    float* sb = reinterpret_cast<float*>(sq + (P - 1) * NB * kWave);
-#pragma unroll
-    for (int p = 0; p + 1 < P; ++p)
-#pragma unroll
-        for (int I = 0; I < NB; ++I) sq[(p * NB + I) * kWave + lane] = qa.q[I][p];
-#pragma unroll
-    for (int I = 0; I < NB; ++I) sb[I * kWave + lane] = qa.b[I];
-    __syncthreads();
-#pragma unroll
-    for (int I = 0; I < NB; ++I) acc[tu(NB, I, NB - 1)] = f4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-    for (int p = 0; p + 1 < P; ++p) {
-        if ((c >> 2) == p) {
-            const int src = 4 * g + (c & 3);
-#pragma unroll
-            for (int I = 0; I < NB; ++I) {
-                const f4* s = sq + (p * NB + I) * kWave + src;
-                acc[tu(NB, I, NB - 1)] = ((s[0] + s[16]) + s[32]) + s[48];
-            }
-        }
-    }
-    if (c == 4 * (P - 1)) {
-#pragma unroll
-        for (int I = 0; I < NB; ++I) {
-            const f4* s = reinterpret_cast<const f4*>(sb + I * kWave + 4 * g);   // slot e: s[4e]
-            acc[tu(NB, I, NB - 1)] = ((s[0] + s[4]) + s[8]) + s[12];
-        }
-    }
-    __syncthreads();
-}
+__device__ __forceinline__ int packed_column(int c, int q) { return c < 3 * q ? c % q : 16; }
 
 // The theta gather of one step, as MFMA operands: lane (g, c) of block I reads
-// theta_{v_g}[16 I + c], and the lane of column f takes the rating.  Three forms (the second
-// template argument):
+// theta_{v_g}[16 I + c] (of a packed last block: the column of packed_column), and the lanes of
+// column f take the rating.  Three forms (the second template argument):
 //   kFormBuffer, for theta below 2 GiB: raw buffer loads against a descriptor that bounds
 //     theta.  The gather word of an entry is its byte offset 4 f v; an entry past the piece's end
 //     gets the buffer size, and the lanes of padding columns add the size to their offset, so
@@ -313,19 +242,17 @@ struct RingEntryT {
     float r;
 };
 
-template <int NB, int BUF, int P = 0>
+template <int NB, int BUF, int LAST = kLastTiles>
 struct Gather;
 
-template <int NB, int P>
-struct Gather<NB, kFormBuffer, P> {
+template <int NB, int LAST>
+struct Gather<NB, kFormBuffer, LAST> {
     using Entry = RingEntryT<int>;
-    static constexpr int kBuf = NB + (P > 1 ? P - 1 : 0);   // operand values per step
+    static constexpr int kBlocks = LAST == kLastRating ? NB - 1 : NB;   // operand values per step
+    static constexpr int kBuf = kBlocks;                                // gathered values per step
     __amdgpu_buffer_rsrc_t rs;
     unsigned fbytes, size, lo, llast;
-    bool jr, jq;
-    // quad form: quads 0..P-2 hold theta columns 16 (NB-1) + 4p + (lane & 3) (all below f), and
-    // quad P-1 holds only the rating, in its first column (f = 16 (NB-1) + 4 (P-1))
-    unsigned lw[P > 1 ? P - 1 : 1];
+    bool jr;
     __device__ __forceinline__ Gather(const float* theta, int64_t n, int f, int c,
                                       float* = nullptr) {
         fbytes = 4u * (unsigned)f;
@@ -333,13 +260,9 @@ struct Gather<NB, kFormBuffer, P> {
         rs = __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(theta), 0, (int)size,
                                                0x00020000);
         lo = 4u * (unsigned)c;
-        const int jlast = 16 * (NB - 1) + c;
+        const int jlast = 16 * (NB - 1) + (LAST == kLastPacked ? packed_column(c, f - 16 * (NB - 1) + 1) : c);
         llast = jlast < f ? 4u * (unsigned)jlast : size;
         jr = jlast == f;
-        jq = (c & 3) == 0;
-#pragma unroll
-        for (int p = 0; p < (P > 1 ? P - 1 : 1); ++p)
-            lw[p] = 4u * (unsigned)(16 * (NB - 1) + 4 * p + (c & 3));
     }
     __device__ __forceinline__ int word(int col, bool valid) const {
         return valid ? (int)((unsigned)col * fbytes) : (int)size;
@@ -350,60 +273,47 @@ struct Gather<NB, kFormBuffer, P> {
         for (int I = 0; I < NB - 1; ++I)
             v[I] = __builtin_bit_cast(
                 float, __builtin_amdgcn_raw_buffer_load_b32(rs, base + 64u * I, 0, 0));
-        v[NB - 1] = __builtin_bit_cast(
-            float, __builtin_amdgcn_raw_buffer_load_b32(rs, (unsigned)e + llast, 0, 0));
-#pragma unroll
-        for (int p = 0; p + 1 < P; ++p)
-            v[NB + p] = __builtin_bit_cast(
-                float, __builtin_amdgcn_raw_buffer_load_b32(rs, (unsigned)e + lw[p], 0, 0));
+        if constexpr (LAST != kLastRating)
+            v[NB - 1] = __builtin_bit_cast(
+                float, __builtin_amdgcn_raw_buffer_load_b32(rs, (unsigned)e + llast, 0, 0));
     }
-    __device__ __forceinline__ void operands(const float (&B)[kBuf], float r, bool,
-                                             float (&v)[NB], float (&w)[P > 0 ? P : 1]) const {
+    __device__ __forceinline__ void operands(const float (&B)[kBuf], float r,
+                                             float (&v)[kBlocks]) const {
 #pragma unroll
         for (int I = 0; I < NB - 1; ++I) v[I] = B[I];
-        v[NB - 1] = jr ? r : B[NB - 1];
-        if constexpr (P > 0) {
-#pragma unroll
-            for (int p = 0; p + 1 < P; ++p) w[p] = B[NB + p];
-            w[P - 1] = jq ? r : 0.f;
-        }
+        if constexpr (LAST != kLastRating) v[NB - 1] = jr ? r : B[NB - 1];
     }
 };
 
 // A row of zeros, read in place of theta_v by the 64-bit gather for entries past a piece's end.
 __device__ float g_zero_row[16 * kMaxNB];
 
-// Gather<NB, kFormGlobal, P>, for any size of theta: 64-bit global loads.  The gather word of an
+// Gather<NB, kFormGlobal, LAST>, for any size of theta: 64-bit global loads.  The gather word of an
 // entry is its row's address (g_zero_row past the piece's end, so such entries gather zeros);
 // lane (g, c) reads block I < NB-1 at that address + 4 (16 I + c), with 64 I as the
 // instruction's immediate offset.  In the last block a padding lane reads a column of the cache
 // line the block's real lanes read -- its first column, or column f - 1 when it has none -- and
-// the value is replaced (by the rating in column f, else by 0); the quad operands read their
-// columns 16 (NB-1) + 4 p + (c & 3) as in the buffer form.
-template <int NB, int P>
-struct Gather<NB, kFormGlobal, P> {
+// the value is replaced (by the rating in column f, else by 0).
+template <int NB, int LAST>
+struct Gather<NB, kFormGlobal, LAST> {
     using Entry = RingEntryT<uint64_t>;
-    static constexpr int kBuf = NB + (P > 1 ? P - 1 : 0);
+    static constexpr int kBlocks = LAST == kLastRating ? NB - 1 : NB;
+    static constexpr int kBuf = kBlocks;
     typedef const __attribute__((address_space(1))) float* gptr;
     uint64_t base, zero;
     unsigned fbytes, lo, llast;
-    bool jpad, jr, jq;
-    unsigned lw[P > 1 ? P - 1 : 1];
+    bool jpad, jr;
     __device__ __forceinline__ Gather(const float* theta, int64_t, int f, int c,
                                       float* = nullptr) {
         base = (uint64_t)theta;
         zero = (uint64_t)g_zero_row;
         fbytes = 4u * (unsigned)f;
         lo = 4u * (unsigned)c;
-        const int jlast = 16 * (NB - 1) + c;
+        const int jlast = 16 * (NB - 1) + (LAST == kLastPacked ? packed_column(c, f - 16 * (NB - 1) + 1) : c);
         jpad = jlast >= f;
         const int jsame = 16 * (NB - 1) < f ? 16 * (NB - 1) : f - 1;
         llast = 4u * (unsigned)(jpad ? jsame : jlast);
         jr = jlast == f;
-        jq = (c & 3) == 0;
-#pragma unroll
-        for (int p = 0; p < (P > 1 ? P - 1 : 1); ++p)
-            lw[p] = 4u * (unsigned)(16 * (NB - 1) + 4 * p + (c & 3));
     }
     __device__ __forceinline__ uint64_t word(int col, bool valid) const {
         return valid ? base + (uint64_t)(unsigned)col * fbytes : zero;
@@ -412,20 +322,13 @@ struct Gather<NB, kFormGlobal, P> {
         const gptr pl = (gptr)(e + lo);
 #pragma unroll
         for (int I = 0; I < NB - 1; ++I) v[I] = pl[16 * I];
-        v[NB - 1] = *(gptr)(e + llast);
-#pragma unroll
-        for (int p = 0; p + 1 < P; ++p) v[NB + p] = *(gptr)(e + lw[p]);
+        if constexpr (LAST != kLastRating) v[NB - 1] = *(gptr)(e + llast);
     }
-    __device__ __forceinline__ void operands(const float (&B)[kBuf], float r, bool,
-                                             float (&v)[NB], float (&w)[P > 0 ? P : 1]) const {
+    __device__ __forceinline__ void operands(const float (&B)[kBuf], float r,
+                                             float (&v)[kBlocks]) const {
 #pragma unroll
         for (int I = 0; I < NB - 1; ++I) v[I] = B[I];
-        v[NB - 1] = jpad ? (jr ? r : 0.f) : B[NB - 1];
-        if constexpr (P > 0) {
-#pragma unroll
-            for (int p = 0; p + 1 < P; ++p) w[p] = B[NB + p];
-            w[P - 1] = jq ? r : 0.f;
-        }
+        if constexpr (LAST != kLastRating) v[NB - 1] = jpad ? (jr ? r : 0.f) : B[NB - 1];
     }
 };
 
@@ -439,9 +342,9 @@ struct Gather<NB, kFormGlobal, P> {
 constexpr int stage_floats(int nb) { return 4 * 16 * nb; }
 
 template <int NB>
-struct Gather<NB, kFormStaged, 0> {
+struct Gather<NB, kFormStaged, kLastTiles> {
     using Entry = RingEntryT<int>;
-    static constexpr int kBuf = 8;
+    static constexpr int kBlocks = NB, kBuf = 8;
     __amdgpu_buffer_rsrc_t rs;
     unsigned fbytes, size, o0, o1;
     int lane;
@@ -472,8 +375,8 @@ struct Gather<NB, kFormStaged, 0> {
             v[4 + j] = b[j];
         }
     }
-    __device__ __forceinline__ void operands(const float (&B)[kBuf], float r, bool,
-                                             float (&v)[NB], float (&)[1]) const {
+    __device__ __forceinline__ void operands(const float (&B)[kBuf], float r,
+                                             float (&v)[NB]) const {
         const int g = lane >> 4, c = lane & 15;
         float* row = stage + g * 16 * NB;
         if (4 * c + 4 <= 16 * NB)
@@ -488,15 +391,15 @@ struct Gather<NB, kFormStaged, 0> {
     }
 };
 
-// Entry `first + lane` of the piece starting at kbeg (lanes below kBatch; past the end: the
+// Entry `first + lane` of the piece starting at kbeg (lanes below BATCH; past the end: the
 // invalid gather word and rating 0).
-template <class G>
+template <int BATCH, class G>
 __device__ __forceinline__ typename G::Entry load_entry(const G& gat,
                                                         const int32_t* __restrict__ colidx,
                                                         const float* __restrict__ vals,
                                                         int64_t kbeg, int64_t total,
                                                         int64_t first, int lane) {
-    const bool valid = lane < kBatch && first + lane < total;
+    const bool valid = lane < BATCH && first + lane < total;
     int col = 0;
     float rv = 0.f;
     if (valid) {
@@ -524,8 +427,8 @@ template <class G>
 __device__ __forceinline__ void gram_prefetch(const G& gat, const int32_t* __restrict__ colidx,
                                               const float* __restrict__ vals, int64_t kbeg,
                                               int64_t kend, int lane, RowIndex<G>& ix) {
-    ix.q0 = load_entry(gat, colidx, vals, kbeg, kend - kbeg, 0, lane);
-    ix.q1 = load_entry(gat, colidx, vals, kbeg, kend - kbeg, kBatch, lane);
+    ix.q0 = load_entry<kBatch>(gat, colidx, vals, kbeg, kend - kbeg, 0, lane);
+    ix.q1 = load_entry<kBatch>(gat, colidx, vals, kbeg, kend - kbeg, kBatch, lane);
 }
 
 // Put a piece's first two batches into ring slots 0 and 1 (the ring must be idle) and issue
@@ -591,10 +494,6 @@ __device__ __forceinline__ void pipe_loop(const G& gat, const int32_t* __restric
     int qb = 0, k = 0;       // group's position in its batch; batch of the group's steps
     int rq = 4 * kDepth;     // ring position of the first step issued in the group
     for (int q = 0; q < ngroups; ++q) {
-        if constexpr (Body::kParts) {
-            // at every part boundary the body folds its accumulators away (see GramBody)
-            if (q > 0 && (q & body.part_mask) == 0) body.flush(q == body.part_mask + 1);
-        }
         // batch k+1 goes into the ring at the top of group 1, one group after its load was
         // issued at the top of group 0 (the store comes first in program order, so its wait
         // never covers the gathers issued after the load)
@@ -603,7 +502,7 @@ __device__ __forceinline__ void pipe_loop(const G& gat, const int32_t* __restric
             __syncthreads();
         }
         if (qb == 0 && k > 0)
-            nq = load_entry(gat, colidx, vals, kbeg, total, (int64_t)(k + 1) * kBatch, lane);
+            nq = load_entry<kBatch>(gat, colidx, vals, kbeg, total, (int64_t)(k + 1) * kBatch, lane);
         pipe_substeps<0>(gat, ring, rq, q * kGroup, total, g, in, body);
         rq += 4 * kGroup;
         if (rq >= kRing) rq -= kRing;
@@ -615,15 +514,160 @@ __device__ __forceinline__ void pipe_loop(const G& gat, const int32_t* __restric
     __syncthreads();   // the ring is refilled by the next piece
 }
 
-// A piece longer than a part (kPart entries by default; a power of two times the 16 entries of a
-// pipeline group) runs in parts (the last one shorter): each part's Gram is accumulated in
+// ---- the Gram: three-way split bf16 products
+//
+// The Gram's products run on the bf16 matrix units with every fp32 value split exactly into three
+// bf16 parts, x = h + m + l (h: the upper 16 bits of x; m, l: the rest rounded to nearest, twice; 8
+// significant bits each), and six of the nine part products kept: hh, hm, mh, mm, hl, lh.  The
+// dropped ml, lm, ll are below 2^-23 of hh, 2^-26 on average and of random sign, under the
+// rounding of an fp32 product sum.  Part products are exact in fp32.  A group of 32 entries is one K = 32
+// step: its products start from zero, smallest parts first, and their sum is added to the fp32
+// accumulator once, so that an accumulator is rounded once per 32 entries (the fp32
+// v_mfma_f32_16x16x4_f32 rounds it for every entry): against fp64 the Gram errs less than the
+// fp32 form at every length.
+//
+// Why: v_mfma_f32_16x16x4_f32 takes 32 cycles for 4 entries of a tile, 256 cycles for 32, and
+// nothing else runs on the SIMD meanwhile (fp32 MFMA and VALU work exclude each other).  Six
+// v_mfma_f32_16x16x32_bf16 take 96, and the other wave's VALU work runs beside them.
+//
+// The gather layout is unchanged: lane (g, c) loads column 16 I + c of entry 4 j + g for step j of
+// the group's eight, and holds, after the split, K slots 8 g + j of its column, which is the bf16
+// operand layout (K slot order is the same for both operands, so any order serves).
+//
+// Registers bound the design (two waves per SIMD, 256 each, for f < 116): 4 per tile for the
+// accumulators, 12 per block for the parts and 8 per block for the gathered values do not fit
+// together at f = 100.  So the columns of tiles are run last first, column J taking the tiles (I, J),
+// I <= J; after it the parts of block J are dead, and their registers take the next group's
+// gathers.  (Splitting the next group's block J beside column J - 1 instead, each block gathered three
+// columns ahead, measured slower: 10.8 against 10.2 ms on the movie user side; the parts then live
+// through the solve.)
+//
+// A packed last block holds, as one operand, the h parts in lanes 0..q-1, the m parts in q..2q-1 and
+// the l parts in 2q..3q-1: three products per tile (by the other operand's l, m and h parts)
+// instead of six, one for the tile (NB-1, NB-1), and 4 registers instead of 12.  The column groups
+// are added when the Gram is complete (fold_packed).
+constexpr int kGroupSteps = 8;
+constexpr int kGroupEntries = 4 * kGroupSteps;
+constexpr int kGramBatch = kWave;              // index batch: one entry per lane, two groups
+constexpr int kGramRing = 2 * kGramBatch;
+
+typedef unsigned u4 __attribute__((ext_vector_type(4)));
+typedef float f2 __attribute__((ext_vector_type(2)));
+typedef __bf16 bf2 __attribute__((ext_vector_type(2)));
+typedef __bf16 bf8 __attribute__((ext_vector_type(8)));
+
+// The three parts of x and y, packed (x in the low half).  h is cut, not rounded, so that no
+// finite value's parts overflow.
+__device__ __forceinline__ void split_pair(float x, float y, unsigned& h, unsigned& m,
+                                           unsigned& l) {
+    const unsigned xb = __builtin_bit_cast(unsigned, x), yb = __builtin_bit_cast(unsigned, y);
+    h = __builtin_amdgcn_perm(yb, xb, 0x07060302u);
+    const float rx = x - __builtin_bit_cast(float, xb & 0xFFFF0000u);
+    const float ry = y - __builtin_bit_cast(float, yb & 0xFFFF0000u);
+    m = __builtin_bit_cast(unsigned, __builtin_convertvector(f2{rx, ry}, bf2));
+    const float sx = rx - __builtin_bit_cast(float, m << 16);
+    const float sy = ry - __builtin_bit_cast(float, m & 0xFFFF0000u);
+    l = __builtin_bit_cast(unsigned, __builtin_convertvector(f2{sx, sy}, bf2));
+}
+
+__device__ __forceinline__ f4 mfma_bf16(u4 a, u4 b, f4 c) {
+    return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf8, a),
+                                                   __builtin_bit_cast(bf8, b), c, 0, 0, 0);
+}
+
+// The parts of a group's operands: element p of a part holds steps 2p and 2p + 1.
+template <int NB, int LAST>
+struct Parts {
+    static constexpr int kFull = LAST == kLastTiles ? NB : NB - 1;   // blocks with three parts
+    u4 h[kFull], m[kFull], l[kFull];
+    u4 last;   // kLastPacked: the last block
+};
+
+// Tiles that the products fill, and the registers of a group's accumulators and parts.
+constexpr int gram_tiles(int nb, int last) { return ntiles(last == kLastRating ? nb - 1 : nb); }
+constexpr int gram_registers(int nb, int last) {
+    return 4 * gram_tiles(nb, last) + 12 * (last == kLastTiles ? nb : nb - 1) +
+           (last == kLastPacked ? 4 : 0) + (last == kLastRating ? nb - 1 : 0);
+}
+// Two waves per SIMD where accumulators and parts leave 50 registers of 256 for the rest.
+constexpr int gram_waves(int nb, int last) { return gram_registers(nb, last) <= 206 ? 2 : 1; }
+
+// The gathered values of a group, step by step.
+template <class G>
+struct Raw {
+    float b[kGroupSteps][G::kBuf];
+};
+
+// Issue the gathers of steps [J0, J1) of the group whose entries start at `ring`.
+template <int J0, int J1, class G>
+__device__ __forceinline__ void issue_steps(const G& gat, const typename G::Entry* ring, int g,
+                                            Raw<G>& raw) {
+#pragma unroll
+    for (int j = J0; j < J1; ++j) gat.issue(ring[4 * j + g].e, raw.b[j]);
+}
+
+// Steps of the next group that may have been issued before column J is run (J = -1: when all are
+// done): as many as the registers left over and the parts of the finished blocks allow.  (A budget
+// of 190 or 200 registers instead of 184 spills: movie user side 10.33 and 10.43 against 9.89 ms;
+// 160 reads the same there and 22% slower with the 64-bit gather.)
+template <int NB, int LAST>
+constexpr int steps_before(int J) {
+    constexpr int top = LAST == kLastRating ? NB - 2 : NB - 1;
+    constexpr int per_step = LAST == kLastRating ? NB - 1 : NB;
+    if (J < 0 || gram_waves(NB, LAST) == 1) return kGroupSteps;
+    int freed = 184 - gram_registers(NB, LAST);
+    for (int k = top; k > J; --k) freed += LAST == kLastPacked && k == NB - 1 ? 4 : 12;
+    const int steps = freed <= 0 ? 0 : freed / per_step;
+    return steps > kGroupSteps ? kGroupSteps : steps;
+}
+
+template <int NB, int LAST, int J, class G>
+__device__ __forceinline__ void tile_columns(const Parts<NB, LAST>& a, f4 (&acc)[ntiles(NB)],
+                                             const G& gat, const typename G::Entry* next, int g,
+                                             Raw<G>& raw) {
+    constexpr f4 zero = f4{0.f, 0.f, 0.f, 0.f};
+    constexpr bool packed = LAST == kLastPacked && J == NB - 1;
+#pragma unroll
+    for (int I0 = 0; I0 <= J; I0 += 2) {   // two chains side by side
+        f4 t[2];
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+            const int I = I0 + i;
+            if (I > J) continue;
+            if constexpr (packed) {
+                if (I == J) {
+                    t[i] = mfma_bf16(a.last, a.last, zero);
+                } else {
+                    t[i] = mfma_bf16(a.l[I], a.last, zero);
+                    t[i] = mfma_bf16(a.m[I], a.last, t[i]);
+                    t[i] = mfma_bf16(a.h[I], a.last, t[i]);
+                }
+            } else {
+                t[i] = mfma_bf16(a.l[I], a.h[J], zero);
+                t[i] = mfma_bf16(a.h[I], a.l[J], t[i]);
+                t[i] = mfma_bf16(a.m[I], a.m[J], t[i]);
+                t[i] = mfma_bf16(a.m[I], a.h[J], t[i]);
+                t[i] = mfma_bf16(a.h[I], a.m[J], t[i]);
+                t[i] = mfma_bf16(a.h[I], a.h[J], t[i]);
+            }
+        }
+#pragma unroll
+        for (int i = 0; i < 2; ++i)
+            if (I0 + i <= J) acc[tu(NB, I0 + i, J)] += t[i];
+    }
+    __builtin_amdgcn_sched_barrier(0);
+    issue_steps<steps_before<NB, LAST>(J), steps_before<NB, LAST>(J - 1)>(gat, next, g, raw);
+    if constexpr (J > 0) tile_columns<NB, LAST, J - 1>(a, acc, gat, next, g, raw);
+}
+
+// A row piece longer than a part (kPart entries by default; a power of two times a group's 32 entries)
+// runs in parts (the last one shorter): each part's Gram is accumulated in
 // registers from zero, and the parts' sums are added in order into the wave's own
 // partial-accumulator slot in the workspace, the second level of a two-level sum, so that no fp32
 // running sum spans more than a part (a column of tens of millions of ratings otherwise
 // accumulates over a million entries in one register chain).  After the last part the slot is
 // added into the registers and the piece goes on as one accumulator.
 constexpr int64_t kPart = 1 << 16;
-constexpr int kEntriesPerGroup = 4 * kGroup;
 
 // A partial-accumulator slot: tile t of lane l at f4 index 64 t + l (16 contiguous bytes per
 // lane, 1 KiB per tile).
@@ -686,107 +730,238 @@ __device__ __forceinline__ void add_slot_in_fours(f4 (&acc)[ntiles(NB)],
     }
 }
 
-// The Gram body: accumulate the upper block-triangle of the augmented Gram matrix into acc
-// (and the quad accumulators of the last block column).  Every kPartGroups groups the pipeline
-// calls flush(): the accumulators so far (the quad ones turned into tiles) are stored into, or
-// added to, the wave's slot, and start again from zero.
-template <int NB, int P>
-__device__ __forceinline__ void zero_quads(QuadAcc<NB, P>& qa) {
-    if constexpr (P > 0) {
+// The column groups of a packed last block (parts h, m, l) into its real columns 0..q-1, the row
+// groups of the tile (NB-1, NB-1) into its real rows, the rest of the tiles zero.
+// scratch: NB KiB of LDS, 16-byte aligned.
+template <int NB>
+__device__ __forceinline__ void fold_packed(f4 (&acc)[ntiles(NB)], int q, void* scratch,
+                                            int lane) {
+    const int g = lane >> 4, c = lane & 15;
+    f4* sc = reinterpret_cast<f4*>(scratch);
 #pragma unroll
-        for (int I = 0; I < NB; ++I) {
+    for (int I = 0; I < NB; ++I) sc[I * kWave + lane] = acc[tu(NB, I, NB - 1)];
+    __syncthreads();
 #pragma unroll
-            for (int p = 0; p + 1 < P; ++p) qa.q[I][p] = f4{0.f, 0.f, 0.f, 0.f};
-            qa.b[I] = 0.f;
+    for (int I = 0; I < NB; ++I) {
+        f4 v = f4{0.f, 0.f, 0.f, 0.f};
+        if (c < q) {
+            const f4* p = sc + I * kWave + lane;
+            v = (p[2 * q] + p[q]) + p[0];
+        }
+        acc[tu(NB, I, NB - 1)] = v;
+    }
+    __syncthreads();
+    // row i of the last tile is element i & 3 of lane (i / 4, c): float 64 (i / 4) + 4 c + (i & 3)
+    float* s = reinterpret_cast<float*>(scratch);
+    *reinterpret_cast<f4*>(s + 4 * lane) = acc[tu(NB, NB - 1, NB - 1)];
+    __syncthreads();
+    f4 v = f4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+        const int i = 4 * g + r;
+        if (i < q && c < q) {
+            const auto at = [&](int row) { return s[64 * (row >> 2) + 4 * c + (row & 3)]; };
+            v[r] = (at(i + 2 * q) + at(i + q)) + at(i);
         }
     }
+    acc[tu(NB, NB - 1, NB - 1)] = v;
+    __syncthreads();
 }
 
-template <int NB, int P, class G, bool PARTS>
+// The rating column's sums (b[I] at lane (e, c): entry slot e's part of M[16 I + c][f]) into column
+// 0 of the last block column's tiles, the rest of those zero.
+template <int NB>
+__device__ __forceinline__ void fold_rating(f4 (&acc)[ntiles(NB)], const float (&b)[NB - 1],
+                                            void* scratch, int lane) {
+    const int g = lane >> 4, c = lane & 15;
+    float* sb = reinterpret_cast<float*>(scratch);
+#pragma unroll
+    for (int I = 0; I < NB - 1; ++I) sb[I * kWave + lane] = b[I];
+    __syncthreads();
+#pragma unroll
+    for (int I = 0; I < NB; ++I) {
+        f4 v = f4{0.f, 0.f, 0.f, 0.f};
+        if (I < NB - 1 && c == 0) {
+            const f4* s = reinterpret_cast<const f4*>(sb + I * kWave + 4 * g);   // slot e: s[4e]
+            v = ((s[0] + s[4]) + s[8]) + s[12];
+        }
+        acc[tu(NB, I, NB - 1)] = v;
+    }
+    __syncthreads();
+}
+
+template <int NB, int LAST, class G, bool PARTS>
 struct GramBody {
     static constexpr bool kParts = PARTS;
+    static constexpr int kTop = LAST == kLastRating ? NB - 2 : NB - 1;   // last column of products
     int part_mask;        // groups per part - 1 (a power of two - 1)
     const G& gat;
     f4 (&acc)[ntiles(NB)];
-    QuadAcc<NB, P>& qa;
-    void* quad_scratch;   // LDS for the quad exchange
+    int q;                // real columns of the last block
+    int third;            // kLastPacked: the part of the last block this lane holds (0: h, 1: m, 2: l)
+    void* scratch;        // LDS for fold_packed and fold_rating
     float* wslot;         // the wave's slot
     int lane;
-    float v[NB], w[P > 0 ? P : 1], r;
-    __device__ __forceinline__ void take(const float (&B)[G::kBuf], float rr, bool ok) {
-        gat.operands(B, rr, ok, v, w);
-        r = rr;   // quad form only (buffer gather: an entry past the end has rating 0)
+    float b[NB > 1 ? NB - 1 : 1];   // kLastRating: the rating column's sums
+    Parts<NB, LAST> a;
+    // the accumulators from zero (those of the last block column are set by finish where no
+    // products fill them)
+    __device__ __forceinline__ void clear() {
+#pragma unroll
+        for (int I = 0; I <= kTop; ++I)
+#pragma unroll
+            for (int J = I; J <= kTop; ++J) acc[tu(NB, I, J)] = f4{0.f, 0.f, 0.f, 0.f};
+        if constexpr (LAST == kLastRating) {
+#pragma unroll
+            for (int I = 0; I < NB - 1; ++I) b[I] = 0.f;
+        }
     }
-    template <int J>
-    __device__ __forceinline__ void run() { mfma_step<NB, P>(v, w, r, acc, qa); }
+    // the group's operands from its gathered values and its ratings (in the ring)
+    __device__ __forceinline__ void take(const Raw<G>& raw, const typename G::Entry* ring) {
+        const int g = lane >> 4;
+#pragma unroll
+        for (int p = 0; p < kGroupSteps / 2; ++p) {
+            float x[G::kBlocks], y[G::kBlocks];
+            const float rx = ring[4 * (2 * p) + g].r, ry = ring[4 * (2 * p + 1) + g].r;
+            gat.operands(raw.b[2 * p], rx, x);
+            gat.operands(raw.b[2 * p + 1], ry, y);
+#pragma unroll
+            for (int I = 0; I < G::kBlocks; ++I) {
+                unsigned h, m, l;
+                split_pair(x[I], y[I], h, m, l);
+                if constexpr (LAST == kLastRating)
+                    b[I] = __builtin_fmaf(y[I], ry, __builtin_fmaf(x[I], rx, b[I]));
+                if (LAST == kLastPacked && I == NB - 1) {
+                    a.last[p] = third == 0 ? h : (third == 1 ? m : l);
+                } else {
+                    a.h[I][p] = h;
+                    a.m[I][p] = m;
+                    a.l[I][p] = l;
+                }
+            }
+        }
+    }
+    __device__ __forceinline__ void run(const typename G::Entry* next, Raw<G>& raw) {
+        issue_steps<0, steps_before<NB, LAST>(kTop)>(gat, next, lane >> 4, raw);
+        tile_columns<NB, LAST, kTop>(a, acc, gat, next, lane >> 4, raw);
+    }
+    __device__ __forceinline__ void finish() {
+        if constexpr (LAST == kLastPacked) fold_packed<NB>(acc, q, scratch, lane);
+        if constexpr (LAST == kLastRating) fold_rating<NB>(acc, b, scratch, lane);
+    }
+    // at a part boundary the accumulators so far are stored into, or added to, the wave's slot,
+    // and start again from zero
     __device__ __forceinline__ void flush(bool first) {
-        if constexpr (P > 0) quad_to_tiles<NB, P>(qa, acc, quad_scratch, lane);
+        finish();
         if (first) store_slot<NB>(acc, wslot, lane);
         else fold_into_slot<NB>(acc, wslot, lane);
-#pragma unroll
-        for (int t = 0; t < ntiles(NB); ++t) acc[t] = f4{0.f, 0.f, 0.f, 0.f};
-        zero_quads<NB, P>(qa);
+        clear();
     }
 };
 
-template <int NB, int P, bool PARTS, class G>
-__device__ __forceinline__ void gram_loop(const G& gat, const int32_t* __restrict__ colidx,
-                                          const float* __restrict__ vals, int64_t kbeg,
-                                          int64_t kend, f4 (&acc)[ntiles(NB)],
-                                          QuadAcc<NB, P>& qa, typename G::Entry* ring, int lane,
-                                          Inflight<G::kBuf>& in, void* quad_scratch,
-                                          float* wslot, int part_mask) {
-    GramBody<NB, P, G, PARTS> body{part_mask, gat, acc, qa, quad_scratch, wslot, lane, {}, {},
-                                   0.f};
-    pipe_loop(gat, colidx, vals, kbeg, kend, ring, lane, in, body);
+// The first batch of a piece into ring slot `slot`, and the gathers of its first group.
+template <class G>
+__device__ __forceinline__ void start_piece(const G& gat, const typename G::Entry& first,
+                                            typename G::Entry* ring, int slot, int lane,
+                                            Raw<G>& raw) {
+    ring[slot * kGramBatch + lane] = first;
+    __syncthreads();
+    issue_steps<0, kGroupSteps>(gat, ring + slot * kGramBatch, lane >> 4, raw);
 }
 
-// The gather stage made visible (test and debug support): for one row, the operands the Gram's
-// MFMAs would receive -- the same Gather form, index ring and pipeline as k_herm_solve -- are
+// Run entries [kbeg, kend) of one row piece, whose first group's gathers are in flight, group by
+// group: the body takes the group's operands (take), then runs its products while the next
+// group's gathers are issued (run).  After the last group those are the next piece's (its first
+// batch, next_first, goes into the ring; without a next piece the last group is gathered once
+// more and not used).  The index batches alternate between the ring's two slots; `slot` is the slot
+// of the piece's first batch, and of the next piece's on return.  Batch k + 1 is loaded (one entry
+// per lane) at batch k's first group and stored at its second, whose run reads it first.
+template <class G, class Body>
+__device__ __forceinline__ void group_loop(const G& gat, const int32_t* __restrict__ colidx,
+                                           const float* __restrict__ vals, int64_t kbeg,
+                                           int64_t kend, typename G::Entry* ring, int& slot,
+                                           int lane, Raw<G>& raw, bool more,
+                                           const typename G::Entry& next_first, Body& body) {
+    // a row has fewer than 2^31 entries (its columns are distinct int32 indices)
+    const int total = (int)(kend - kbeg);
+    const int ngroups = (total + kGroupEntries - 1) / kGroupEntries;
+    typename G::Entry nq{};
+    for (int q = 0; q < ngroups; ++q) {
+        if constexpr (Body::kParts) {
+            if (q > 0 && (q & body.part_mask) == 0) body.flush(q == body.part_mask + 1);
+        }
+        const int other = slot ^ 1;   // `slot` holds this group's batch
+        const int odd = q & 1;
+        const typename G::Entry* cur = ring + slot * kGramBatch + odd * kGroupEntries;
+        const bool last = q + 1 == ngroups;
+        if (!odd && !last)
+            nq = load_entry<kGramBatch>(gat, colidx, vals, kbeg, total,
+                                        (int64_t)(q / 2 + 1) * kGramBatch, lane);
+        body.take(raw, cur);
+        const typename G::Entry* next = odd ? cur : cur + kGroupEntries;
+        if (last) next = cur;
+        if (last ? more : odd) {
+            ring[other * kGramBatch + lane] = last ? next_first : nq;
+            __syncthreads();
+            next = ring + other * kGramBatch;
+        }
+        body.run(next, raw);
+        if (last || odd) slot = other;
+    }
+}
+
+// The gather stage made visible (test and debug support): for one row, the values the Gram's
+// operands are split from -- the same Gather form, index ring and group loop as k_herm_solve -- are
 // written out per entry instead of multiplied.  Entry k's record has 16 (NB + 3) floats: block I
-// of the MFMA operand at 16 I + c (lane c of the entry's 16-lane group), the quad operands w[p] at
-// 16 (NB + p) + c (quad form only; untouched otherwise), and the rating the body uses at
-// 16 (NB + 2) + c.
+// of the operand at 16 I + c (lane c of the entry's 16-lane group, zero in the second and third
+// copies of a packed block's columns; the rating where the rating column has no block); for f mod 16 =
+// 0 or 4, unless the last block is an ordinary one, its columns by quads, lane c holding column c & 3
+// of the quad, at 16 (NB + p) + c (untouched otherwise); and the rating at 16 (NB + 2) + c.
 template <int NB>
 constexpr int dump_floats() { return 16 * (NB + 3); }
 
-template <int NB, int P, class G>
+template <int NB, int LAST, class G>
 struct DumpBody {
     static constexpr bool kParts = false;
     const G& gat;
     float* __restrict__ out;
     int64_t limit;   // entries that fit in out
-    int total, lane, step;
-    float v[NB], w[P > 0 ? P : 1], r;
-    __device__ __forceinline__ void take(const float (&B)[G::kBuf], float rr, bool ok) {
-        gat.operands(B, rr, ok, v, w);
-        r = rr;
-    }
-    template <int J>
-    __device__ __forceinline__ void run() {
+    int q, total, lane, group;
+    __device__ __forceinline__ void take(const Raw<G>& raw, const typename G::Entry* ring) {
         const int g = lane >> 4, c = lane & 15;
-        const int64_t k = 4 * (int64_t)step + g;
-        if (k < total && k < limit) {
-            float* rec = out + k * dump_floats<NB>();
 #pragma unroll
-            for (int I = 0; I < NB; ++I) rec[16 * I + c] = v[I];
-            if constexpr (P > 0) {
+        for (int j = 0; j < kGroupSteps; ++j) {
+            const float r = ring[4 * j + g].r;
+            float v[G::kBlocks];
+            gat.operands(raw.b[j], r, v);
+            const float quad = __shfl(v[G::kBlocks - 1], (lane & 48) | (c & 3));
+            const int64_t k = (int64_t)kGroupEntries * group + 4 * j + g;
+            if (k < total && k < limit) {
+                float* rec = out + k * dump_floats<NB>();
 #pragma unroll
-                for (int p = 0; p < P; ++p) rec[16 * (NB + p) + c] = w[p];
+                for (int I = 0; I < NB - 1; ++I) rec[16 * I + c] = v[I];
+                if constexpr (LAST == kLastRating) rec[16 * (NB - 1) + c] = c == 0 ? r : 0.f;
+                else rec[16 * (NB - 1) + c] = LAST == kLastTiles || c < q ? v[NB - 1] : 0.f;
+                if (LAST == kLastPacked && q == 5) rec[16 * NB + c] = quad;
+                if (LAST == kLastRating || (LAST == kLastPacked && q == 5))
+                    rec[16 * (NB + q / 4) + c] = (c & 3) == 0 ? r : 0.f;
+                rec[16 * (NB + 2) + c] = r;
             }
-            rec[16 * (NB + 2) + c] = r;
         }
-        ++step;
+        ++group;
+    }
+    __device__ __forceinline__ void run(const typename G::Entry* next, Raw<G>& raw) {
+        issue_steps<0, kGroupSteps>(gat, next, lane >> 4, raw);
     }
 };
 
-template <int NB, int BUF, int P>
+template <int NB, int BUF, int LAST>
 __global__ __launch_bounds__(kWave) void k_gather_dump(
     const int64_t* __restrict__ rowptr, const int32_t* __restrict__ colidx,
     const float* __restrict__ vals, const float* __restrict__ theta, int64_t n, int f, int64_t u,
     float* __restrict__ out, int64_t limit) {
-    using G = Gather<NB, BUF, P>;
-    __shared__ typename G::Entry ring[kRing];
+    using G = Gather<NB, BUF, LAST>;
+    __shared__ typename G::Entry ring[kGramRing];
     __shared__ __attribute__((aligned(16))) float stage[BUF == kFormStaged ? stage_floats(NB) : 4];
     const int lane = threadIdx.x;
     if constexpr (BUF == kFormStaged) {
@@ -795,12 +970,14 @@ __global__ __launch_bounds__(kWave) void k_gather_dump(
     }
     const G gat(theta, n, f, lane & 15, stage);
     const int64_t kbeg = rowptr[u], kend = rowptr[u + 1];
-    RowIndex<G> ix;
-    Inflight<G::kBuf> in;
-    gram_prefetch(gat, colidx, vals, kbeg, kend, lane, ix);
-    gram_stage(gat, ix, ring, lane, in);
-    DumpBody<NB, P, G> body{gat, out, limit, (int)(kend - kbeg), lane, 0, {}, {}, 0.f};
-    pipe_loop(gat, colidx, vals, kbeg, kend, ring, lane, in, body);
+    if (kbeg == kend) return;
+    const typename G::Entry first =
+        load_entry<kGramBatch>(gat, colidx, vals, kbeg, kend - kbeg, 0, lane);
+    Raw<G> raw;
+    int slot = 0;
+    start_piece(gat, first, ring, slot, lane, raw);
+    DumpBody<NB, LAST, G> body{gat, out, limit, f - 16 * (NB - 1) + 1, (int)(kend - kbeg), lane, 0};
+    group_loop(gat, colidx, vals, kbeg, kend, ring, slot, lane, raw, false, first, body);
 }
 
 // ------------------------------------------------------------------ solve in registers ---
@@ -1149,8 +1326,8 @@ __device__ __forceinline__ int claim_chunk(unsigned* __restrict__ ctr, int strip
     return __builtin_amdgcn_readfirstlane((int)got) * stripes + stripe;
 }
 
-template <int NB, int BUF, int P, bool PARTS>
-__global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(NB <= 8 ? 2 : 1)))
+template <int NB, int BUF, int LAST, bool PARTS>
+__global__ __launch_bounds__(kWave) __attribute__((amdgpu_waves_per_eu(gram_waves(NB, LAST))))
 void k_herm_solve(
     const int64_t* __restrict__ rowptr, const int32_t* __restrict__ colidx,
     const float* __restrict__ vals, const float* __restrict__ theta, int64_t m, int64_t n,
@@ -1165,18 +1342,21 @@ void k_herm_solve(
         const int64_t T = kCostPerEntry * rowptr[m] + c_row * m;
         int64_t longest = (T / (int64_t)gridDim.x + 1) / kCostPerEntry + 2 * kSnap + 1;
         if (longest > n) longest = n;
-        if ((longest > (int64_t)kEntriesPerGroup * (part_mask + 1)) != PARTS) return;
+        if ((longest > (int64_t)kGroupEntries * (part_mask + 1)) != PARTS) return;
     }
-    using G = Gather<NB, BUF, P>;
+    using G = Gather<NB, BUF, LAST>;
     __shared__ __attribute__((aligned(16))) SolveLds<NB> lds;
-    __shared__ typename G::Entry ring[kRing];
+    __shared__ typename G::Entry ring[kGramRing];
     __shared__ __attribute__((aligned(16))) float stage[BUF == kFormStaged ? stage_floats(NB) : 4];
     const int lane = threadIdx.x;
     if constexpr (BUF == kFormStaged) {
         for (int i = lane; i < stage_floats(NB); i += kWave) stage[i] = 0.f;
         __syncthreads();
     }
-    const Gather<NB, BUF, P> gat(theta, n, f, lane & 15, stage);
+    const G gat(theta, n, f, lane & 15, stage);
+    const int q = f - 16 * (NB - 1) + 1, third = (lane & 15) / q;
+    static_assert(NB * kWave * sizeof(f4) <= sizeof(SolveLds<NB>),
+                  "fold_packed and fold_rating reuse the solve's LDS");
     float* __restrict__ wslot = wave_slots + (size_t)blockIdx.x * slot_floats(NB);
     // No lane-0-only region in the claim loop: every lane takes part in a claim, and the wave's
     // count of non-SPD rows stays in a register until the
@@ -1230,30 +1410,26 @@ void k_herm_solve(
         };
         Piece cur;
         if (!next_piece(u0, cur)) continue;
-        RowIndex<G> ix;
-        Inflight<G::kBuf> in;
-        gram_prefetch(gat, colidx, vals, cur.beg, cur.end, lane, ix);
-        gram_stage(gat, ix, ring, lane, in);
+        typename G::Entry first_batch =
+            load_entry<kGramBatch>(gat, colidx, vals, cur.beg, cur.end - cur.beg, 0, lane);
+        Raw<G> raw;
+        int slot = 0;
+        start_piece(gat, first_batch, ring, slot, lane, raw);
         for (;;) {
             Piece nxt;
             const bool more = next_piece(cur.u + 1, nxt);
-            if (more) gram_prefetch(gat, colidx, vals, nxt.beg, nxt.end, lane, ix);
+            if (more)
+                first_batch =
+                    load_entry<kGramBatch>(gat, colidx, vals, nxt.beg, nxt.end - nxt.beg, 0, lane);
             f4 acc[ntiles(NB)];
-#pragma unroll
-            for (int t = 0; t < ntiles(NB); ++t) acc[t] = f4{0.f, 0.f, 0.f, 0.f};
-            QuadAcc<NB, P> qa;
-            zero_quads<NB, P>(qa);
-            gram_loop<NB, P, PARTS>(gat, colidx, vals, cur.beg, cur.end, acc, qa, ring, lane,
-                                    in, &lds, wslot, part_mask);
-            if (more) gram_stage(gat, ix, ring, lane, in);
-            if constexpr (P > 0) {
-                static_assert(quad_scratch_bytes<NB, P>() <= sizeof(SolveLds<NB>),
-                              "the quad exchange reuses the solve's LDS");
-                quad_to_tiles<NB, P>(qa, acc, &lds, lane);
-            }
+            GramBody<NB, LAST, G, PARTS> body{part_mask, gat, acc, q, third, &lds, wslot, lane};
+            body.clear();
+            group_loop(gat, colidx, vals, cur.beg, cur.end, ring, slot, lane, raw, more,
+                       first_batch, body);
+            body.finish();
             // a piece longer than a part: its earlier parts' sum is in the wave's slot
             if constexpr (PARTS) {
-                if (cur.end - cur.beg > (int64_t)kEntriesPerGroup * (part_mask + 1))
+                if (cur.end - cur.beg > (int64_t)kGroupEntries * (part_mask + 1))
                     add_slot_in_fours<NB>(acc, wslot, lane);
             }
             // the solve is a latency-bound chain; raised priority lets it win issue slots over
@@ -1452,15 +1628,14 @@ __global__ __launch_bounds__(kWave) void k_reduce_solve(
 // rating that the gather puts in column f).
 template <int NB, class G>
 struct RmseBody {
-    static constexpr bool kParts = false;
     const G& gat;
     const float (&xr)[NB];
     double& acc;
     bool lead;
-    float v[NB], w[1], r;
+    float v[NB], r;
     float sq;   // this group's squares so far
     __device__ __forceinline__ void take(const float (&B)[G::kBuf], float rr, bool ok) {
-        gat.operands(B, rr, ok, v, w);
+        gat.operands(B, rr, v);
         r = ok ? rr : 0.f;
     }
     template <int J>
@@ -1489,7 +1664,7 @@ __global__ __launch_bounds__(kWave) void k_rmse_rows(
     const float* __restrict__ vals, int64_t m, int64_t n, int f, const float* __restrict__ x,
     const float* __restrict__ theta, int C, double* __restrict__ partial,
     unsigned* __restrict__ claim) {
-    using G = Gather<NB, BUF ? kFormBuffer : kFormGlobal, 0>;
+    using G = Gather<NB, BUF ? kFormBuffer : kFormGlobal>;
     __shared__ typename G::Entry ring[kRing];
     const int lane = threadIdx.x, c = lane & 15;
     const int64_t nnz = rowptr[m];
@@ -1539,7 +1714,7 @@ __global__ __launch_bounds__(kWave) void k_rmse_rows(
                     const int j = 16 * I + c;
                     xr[I] = j < f ? x[(size_t)u * (size_t)f + j] : 0.f;
                 }
-                RmseBody<NB, G> body{gat, xr, acc, c == 0, {}, {}, 0.f, 0.f};
+                RmseBody<NB, G> body{gat, xr, acc, c == 0, {}, 0.f, 0.f};
                 pipe_loop(gat, colidx, vals, pb, pe, ring, lane, in, body);
                 if (!more) break;
                 gram_stage(gat, ix, ring, lane, in);
@@ -1837,18 +2012,22 @@ struct Layout {
 
 size_t align256(size_t x) { return (x + 255) & ~size_t(255); }
 
-// waves[nb] = W for f in (16 (nb-1), 16 nb]; the slot region holds 2 C partial accumulators,
+// waves[nb][last] = W for nb column blocks and a form of the last one (0 where f has no such form);
+// the slot region holds 2 C partial accumulators,
 // C = chunks_of(W), and the wave-slot region one more per wave (the second summation level of
 // long pieces)
-Layout make_layout(const int* waves, int nb_max, int cus) {
+Layout make_layout(const int (*waves)[kLastForms], int nb_max, int cus) {
     int c_cap = 1;
     size_t slot_bytes = 0, wave_bytes = 0;
     for (int nb = 1; nb <= nb_max; ++nb) {
-        const int C = chunks_of(waves[nb]);
+        int w = 0;
+        for (int last = 0; last < kLastForms; ++last)
+            if (waves[nb][last] > w) w = waves[nb][last];
+        const int C = chunks_of(w);
         if (C > c_cap) c_cap = C;
         const size_t sb = sizeof(float) * (size_t)slot_floats(nb) * 2 * (size_t)C;
         if (sb > slot_bytes) slot_bytes = sb;
-        const size_t wb = sizeof(float) * (size_t)slot_floats(nb) * (size_t)waves[nb];
+        const size_t wb = sizeof(float) * (size_t)slot_floats(nb) * (size_t)w;
         if (wb > wave_bytes) wave_bytes = wb;
     }
     Layout L;
@@ -1863,43 +2042,42 @@ Layout make_layout(const int* waves, int nb_max, int cus) {
     return L;
 }
 
+// Whether some f <= ALS_F_MAX with nb column blocks runs with this form of the last one (ordinary
+// tiles can be asked for at every f).
+constexpr bool last_exists(int nb, int last) {
+    if (last == kLastTiles) return true;
+    return last == kLastRating ? nb >= 2 : 16 * (nb - 1) + 1 <= ALS_F_MAX;
+}
+
 // Resident waves per CU of both gather forms (the partition is shared, so every wave of either
 // form is resident at once).
-template <int NB>
-int occupancy_waves(int cus, int* waves) {
-    int blocks = 1 << 30;
-    const void* forms[] = {(const void*)k_herm_solve<NB, kFormBuffer, 0, false>,
-                           (const void*)k_herm_solve<NB, kFormBuffer, 1, false>,
-                           kQuad2<NB> ? (const void*)k_herm_solve<NB, kFormBuffer,
-                                                                  kQuad2<NB> ? 2 : 1, false>
-                                      : nullptr,
-                           (const void*)k_herm_solve<NB, kFormGlobal, 0, false>,
-                           (const void*)k_herm_solve<NB, kFormGlobal, 1, false>,
-                           kQuad2<NB> ? (const void*)k_herm_solve<NB, kFormGlobal,
-                                                                  kQuad2<NB> ? 2 : 1, false>
-                                      : nullptr,
-                           (const void*)k_herm_solve<NB, kFormBuffer, 0, true>,
-                           (const void*)k_herm_solve<NB, kFormBuffer, 1, true>,
-                           kQuad2<NB> ? (const void*)k_herm_solve<NB, kFormBuffer,
-                                                                  kQuad2<NB> ? 2 : 1, true>
-                                      : nullptr,
-                           (const void*)k_herm_solve<NB, kFormGlobal, 0, true>,
-                           (const void*)k_herm_solve<NB, kFormGlobal, 1, true>,
-                           kQuad2<NB> ? (const void*)k_herm_solve<NB, kFormGlobal,
-                                                                  kQuad2<NB> ? 2 : 1, true>
-                                      : nullptr};
-    for (const void* k : forms) {
-        if (!k) continue;
-        int b = 0;
-        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&b, k, kWave, 0) != hipSuccess) return -1;
-        if (b < blocks) blocks = b;
+template <int NB, int LAST>
+int occupancy_waves(int* waves) {
+    *waves = 0;
+    if constexpr (last_exists(NB, LAST)) {
+        int blocks = kMaxWavesPerCU;
+        const void* forms[] = {(const void*)k_herm_solve<NB, kFormBuffer, LAST, false>,
+                               (const void*)k_herm_solve<NB, kFormGlobal, LAST, false>,
+                               (const void*)k_herm_solve<NB, kFormBuffer, LAST, true>,
+                               (const void*)k_herm_solve<NB, kFormGlobal, LAST, true>};
+        for (const void* k : forms) {
+            int b = 0;
+            if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&b, k, kWave, 0) != hipSuccess)
+                return -1;
+            if (b < blocks) blocks = b;
+        }
+        if (blocks < 1) blocks = 1;
+        *waves = blocks;
     }
-    if (blocks < 1) blocks = 1;
-    if (blocks > kMaxWavesPerCU) blocks = kMaxWavesPerCU;
-    const char* env = getenv("ALS_WAVES_PER_CU");
-    if (env && atoi(env) > 0) blocks = atoi(env) < blocks ? atoi(env) : blocks;
-    *waves = blocks * cus;
     return 0;
+}
+
+template <int NB>
+int occupancy_forms(int* waves) {
+    if (occupancy_waves<NB, kLastTiles>(waves + kLastTiles) != 0 ||
+        occupancy_waves<NB, kLastPacked>(waves + kLastPacked) != 0)
+        return -1;
+    return occupancy_waves<NB, kLastRating>(waves + kLastRating);
 }
 
 // Launch the RMSE partials kernel over C = cus * kRmseWavesPerCU chunks (the partials buffer
@@ -1924,17 +2102,17 @@ hipError_t rmse_rows_launch(int cus, int cap_per_cu, hipStream_t st, const int64
     return hipGetLastError();
 }
 
-int waves_for_nb(int nb, int cus, int* w) {
+int waves_per_cu(int nb, int* w) {
     switch (nb) {
-        case 1: return occupancy_waves<1>(cus, w);
-        case 2: return occupancy_waves<2>(cus, w);
-        case 3: return occupancy_waves<3>(cus, w);
-        case 4: return occupancy_waves<4>(cus, w);
-        case 5: return occupancy_waves<5>(cus, w);
-        case 6: return occupancy_waves<6>(cus, w);
-        case 7: return occupancy_waves<7>(cus, w);
-        case 8: return occupancy_waves<8>(cus, w);
-        case 9: return occupancy_waves<9>(cus, w);
+        case 1: return occupancy_forms<1>(w);
+        case 2: return occupancy_forms<2>(w);
+        case 3: return occupancy_forms<3>(w);
+        case 4: return occupancy_forms<4>(w);
+        case 5: return occupancy_forms<5>(w);
+        case 6: return occupancy_forms<6>(w);
+        case 7: return occupancy_forms<7>(w);
+        case 8: return occupancy_forms<8>(w);
+        case 9: return occupancy_forms<9>(w);
         default: return -1;
     }
 }
@@ -1943,11 +2121,13 @@ template <int NB>
 int staged_occupancy(int cus, int* waves) {
     int b = 0;
     if (hipOccupancyMaxActiveBlocksPerMultiprocessor(
-            &b, (const void*)k_herm_solve<NB, kFormStaged, 0, true>, kWave, 0) != hipSuccess)
+            &b, (const void*)k_herm_solve<NB, kFormStaged, kLastTiles, true>, kWave, 0) !=
+        hipSuccess)
         return -1;
     int b2 = 0;
     if (hipOccupancyMaxActiveBlocksPerMultiprocessor(
-            &b2, (const void*)k_herm_solve<NB, kFormStaged, 0, false>, kWave, 0) != hipSuccess)
+            &b2, (const void*)k_herm_solve<NB, kFormStaged, kLastTiles, false>, kWave, 0) !=
+        hipSuccess)
         return -1;
     if (b2 < b) b = b2;
     if (b < 1) b = 1;
@@ -2000,7 +2180,7 @@ struct als_ctx {
     int f_max;
     int nb_max;
     int w_cap;
-    int waves[kMaxNB + 1];
+    int waves[kMaxNB + 1][kLastForms];
     unsigned char* ws;
     size_t ws_bytes;
     Layout lay;
@@ -2036,22 +2216,49 @@ struct DeviceGuard {
     }
 };
 
-int query_device(int device, int f_max, int* cus, int* waves, int* w_cap,
+// What a device is and how many waves of each kernel fit it: asked for once per device and process
+// (with the queries in every call, als_workspace_bytes and als_init took 46 us together, now 28).  Column-block counts are added as they are needed.
+struct DeviceInfo {
+    std::mutex mu;
+    bool known = false;
+    int cus = 0;
+    size_t lds_per_block = 0;
+    int nb_known = 0;                            // per_cu holds 1..nb_known
+    int per_cu[kMaxNB + 1][kLastForms] = {{0}};  // resident waves per CU
+};
+constexpr int kMaxDevices = 64;
+DeviceInfo g_device[kMaxDevices];
+
+int query_device(int device, int f_max, int* cus, int (*waves)[kLastForms], int* w_cap,
                  size_t* lds_per_block = nullptr) {
     int n = 0;
-    if (hipGetDeviceCount(&n) != hipSuccess || device < 0 || device >= n) return ALS_ERR_DEVICE;
-    hipDeviceProp_t prop;
-    if (hipGetDeviceProperties(&prop, device) != hipSuccess) return ALS_ERR_DEVICE;
-    if (strncmp(prop.gcnArchName, "gfx950", 6) != 0) return ALS_ERR_DEVICE;
-    *cus = prop.multiProcessorCount;
-    if (lds_per_block) *lds_per_block = prop.sharedMemPerBlock;
+    if (hipGetDeviceCount(&n) != hipSuccess || device < 0 || device >= n || device >= kMaxDevices)
+        return ALS_ERR_DEVICE;
+    DeviceInfo& d = g_device[device];
+    std::lock_guard<std::mutex> lock(d.mu);
     DeviceGuard guard(device);
     if (!guard.ok) return ALS_ERR_DEVICE;
-    *w_cap = 1;
-    for (int nb = 1; nb <= nb_of(f_max); ++nb) {
-        if (waves_for_nb(nb, *cus, &waves[nb]) != 0) return ALS_ERR_HIP;
-        if (waves[nb] > *w_cap) *w_cap = waves[nb];
+    if (!d.known) {
+        hipDeviceProp_t prop;
+        if (hipGetDeviceProperties(&prop, device) != hipSuccess) return ALS_ERR_DEVICE;
+        if (strncmp(prop.gcnArchName, "gfx950", 6) != 0) return ALS_ERR_DEVICE;
+        d.cus = prop.multiProcessorCount;
+        d.lds_per_block = prop.sharedMemPerBlock;
+        d.known = true;
     }
+    for (; d.nb_known < nb_of(f_max); ++d.nb_known)
+        if (waves_per_cu(d.nb_known + 1, d.per_cu[d.nb_known + 1]) != 0) return ALS_ERR_HIP;
+    *cus = d.cus;
+    if (lds_per_block) *lds_per_block = d.lds_per_block;
+    const char* env = getenv("ALS_WAVES_PER_CU");
+    const int limit = env && atoi(env) > 0 ? atoi(env) : kMaxWavesPerCU;
+    *w_cap = 1;
+    for (int nb = 1; nb <= nb_of(f_max); ++nb)
+        for (int last = 0; last < kLastForms; ++last) {
+            const int w = d.per_cu[nb][last];
+            waves[nb][last] = (w < limit ? w : limit) * d.cus;
+            if (waves[nb][last] > *w_cap) *w_cap = waves[nb][last];
+        }
     return ALS_OK;
 }
 
@@ -2063,6 +2270,11 @@ constexpr uint64_t kBufferGatherMax = 0x7FFFF000ull;
 // descriptor.
 bool staged_supported(int64_t n, int f) {
     return f % 4 == 0 && (uint64_t)n * (uint64_t)f * sizeof(float) <= kBufferGatherMax;
+}
+
+// The form of the last block column that a half-sweep of this context uses at f.
+int form_of(const als_ctx* ctx, int f) {
+    return ctx->staged_gather || ctx->tile_last_block ? kLastTiles : last_form(f);
 }
 
 struct HermArgs {
@@ -2087,17 +2299,29 @@ struct HermArgs {
 // A row has at most n entries (its columns are distinct), so with n no longer than a part no piece
 // is.  Beyond that both instantiations are launched; the kernels pick the one that runs from
 // rowptr[m] on the device (no host synchronisation), the other returns at once (about 5 us).
-template <int NB, int BUF, int P>
+template <int NB, int BUF, int LAST>
 void launch_herm(int W, hipStream_t st, const HermArgs& a) {
-    hipLaunchKernelGGL((k_herm_solve<NB, BUF, P, false>), dim3(W), dim3(kWave), 0, st,
+    hipLaunchKernelGGL((k_herm_solve<NB, BUF, LAST, false>), dim3(W), dim3(kWave), 0, st,
                        a.rowptr, a.colidx, a.vals, a.theta, a.m, a.n, a.f, a.lambda, a.C,
                        a.bounds, a.x, a.slots, a.wslots, a.part_mask, a.c_row, a.nonspd,
                        a.chunk_ctr);
-    if (a.n <= (int64_t)kEntriesPerGroup * (a.part_mask + 1)) return;
-    hipLaunchKernelGGL((k_herm_solve<NB, BUF, P, true>), dim3(W), dim3(kWave), 0, st,
+    if (a.n <= (int64_t)kGroupEntries * (a.part_mask + 1)) return;
+    hipLaunchKernelGGL((k_herm_solve<NB, BUF, LAST, true>), dim3(W), dim3(kWave), 0, st,
                        a.rowptr, a.colidx, a.vals, a.theta, a.m, a.n, a.f, a.lambda, a.C,
                        a.bounds, a.x, a.slots, a.wslots, a.part_mask, a.c_row, a.nonspd,
                        a.chunk_ctr);
+}
+
+// fn with the form of the last block column as a constant.
+template <int NB, class Fn>
+void with_last_form(int last, Fn&& fn) {
+    if (last == kLastTiles) fn(std::integral_constant<int, kLastTiles>{});
+    if constexpr (last_exists(NB, kLastPacked)) {
+        if (last == kLastPacked) fn(std::integral_constant<int, kLastPacked>{});
+    }
+    if constexpr (last_exists(NB, kLastRating)) {
+        if (last == kLastRating) fn(std::integral_constant<int, kLastRating>{});
+    }
 }
 
 template <int NB>
@@ -2117,32 +2341,17 @@ void launch_sweep(als_ctx* ctx, const int64_t* rowptr, const int32_t* colidx, co
     hipLaunchKernelGGL(k_plan, dim3((C + 1 + 63) / 64), dim3(64), 0, st, rowptr, m, W, C,
                        (int64_t)kCostPerEntry, row_cost(f), (int64_t)kSnap, bounds, chunk_ctr);
     if (ev) (void)hipEventRecord(ev[1], st);
-    // the quad form of the last block column: when its theta columns fill whole quads (none or
-    // one) and the rating starts a quad of its own
-    const int f_last = f - 16 * (NB - 1);
-    const int quads =
-        (!ctx->tile_last_block && (f_last == 0 || f_last == 4)) ? f_last / 4 + 1 : 0;
     const HermArgs a{rowptr, colidx, vals, theta, m, n, f, lambda, C, bounds, x, slots, wslots,
                      part_mask, row_cost(f), nonspd, chunk_ctr};
+    const bool buf = !ctx->global_gather &&
+                     (uint64_t)n * (uint64_t)f * sizeof(float) <= kBufferGatherMax;
     if (ctx->staged_gather) {   // f % 4 == 0 and theta below 2 GiB (checked by the caller)
-        launch_herm<NB, kFormStaged, 0>(W, st, a);
-    } else if (!ctx->global_gather &&
-               (uint64_t)n * (uint64_t)f * sizeof(float) <= kBufferGatherMax) {
-        if (quads == 1) {
-            launch_herm<NB, kFormBuffer, 1>(W, st, a);
-        } else if (quads == 2) {
-            if constexpr (kQuad2<NB>) launch_herm<NB, kFormBuffer, 2>(W, st, a);
-        } else {
-            launch_herm<NB, kFormBuffer, 0>(W, st, a);
-        }
+        launch_herm<NB, kFormStaged, kLastTiles>(W, st, a);
     } else {
-        if (quads == 1) {
-            launch_herm<NB, kFormGlobal, 1>(W, st, a);
-        } else if (quads == 2) {
-            if constexpr (kQuad2<NB>) launch_herm<NB, kFormGlobal, 2>(W, st, a);
-        } else {
-            launch_herm<NB, kFormGlobal, 0>(W, st, a);
-        }
+        with_last_form<NB>(form_of(ctx, f), [&](auto last) {
+            if (buf) launch_herm<NB, kFormBuffer, last.value>(W, st, a);
+            else launch_herm<NB, kFormGlobal, last.value>(W, st, a);
+        });
     }
     if (ev) (void)hipEventRecord(ev[2], st);
     if (C > 1) {
@@ -2155,41 +2364,25 @@ void launch_sweep(als_ctx* ctx, const int64_t* rowptr, const int32_t* colidx, co
     if (ev) (void)hipEventRecord(ev[3], st);
 }
 
-// The gather form k_herm_solve would use for this call (buffer loads or 64-bit loads; quad form or
-// tiles for the last block column), run by k_gather_dump on row u.
+// The gather form k_herm_solve would use for this call (buffer loads or 64-bit loads; the form of the
+// last block column), run by k_gather_dump on row u.
 template <int NB>
 void launch_dump(als_ctx* ctx, const int64_t* rowptr, const int32_t* colidx, const float* vals,
                  int64_t n, int f, const float* theta, int64_t u, float* out, int64_t limit,
                  hipStream_t st) {
-    const int f_last = f - 16 * (NB - 1);
-    const int quads =
-        (!ctx->tile_last_block && (f_last == 0 || f_last == 4)) ? f_last / 4 + 1 : 0;
+    const bool buf = !ctx->global_gather &&
+                     (uint64_t)n * (uint64_t)f * sizeof(float) <= kBufferGatherMax;
+    const auto launch = [&](auto kernel) {
+        hipLaunchKernelGGL(kernel, dim3(1), dim3(kWave), 0, st, rowptr, colidx, vals, theta, n, f,
+                           u, out, limit);
+    };
     if (ctx->staged_gather) {
-        hipLaunchKernelGGL((k_gather_dump<NB, kFormStaged, 0>), dim3(1), dim3(kWave), 0, st,
-                           rowptr, colidx, vals, theta, n, f, u, out, limit);
-    } else if (!ctx->global_gather &&
-               (uint64_t)n * (uint64_t)f * sizeof(float) <= kBufferGatherMax) {
-        if (quads == 1)
-            hipLaunchKernelGGL((k_gather_dump<NB, kFormBuffer, 1>), dim3(1), dim3(kWave), 0, st, rowptr,
-                               colidx, vals, theta, n, f, u, out, limit);
-        else if (quads == 2) {
-            if constexpr (kQuad2<NB>)
-                hipLaunchKernelGGL((k_gather_dump<NB, kFormBuffer, 2>), dim3(1), dim3(kWave), 0, st,
-                                   rowptr, colidx, vals, theta, n, f, u, out, limit);
-        } else
-            hipLaunchKernelGGL((k_gather_dump<NB, kFormBuffer, 0>), dim3(1), dim3(kWave), 0, st, rowptr,
-                               colidx, vals, theta, n, f, u, out, limit);
+        launch(k_gather_dump<NB, kFormStaged, kLastTiles>);
     } else {
-        if (quads == 1)
-            hipLaunchKernelGGL((k_gather_dump<NB, kFormGlobal, 1>), dim3(1), dim3(kWave), 0, st,
-                               rowptr, colidx, vals, theta, n, f, u, out, limit);
-        else if (quads == 2) {
-            if constexpr (kQuad2<NB>)
-                hipLaunchKernelGGL((k_gather_dump<NB, kFormGlobal, 2>), dim3(1), dim3(kWave), 0,
-                                   st, rowptr, colidx, vals, theta, n, f, u, out, limit);
-        } else
-            hipLaunchKernelGGL((k_gather_dump<NB, kFormGlobal, 0>), dim3(1), dim3(kWave), 0, st,
-                               rowptr, colidx, vals, theta, n, f, u, out, limit);
+        with_last_form<NB>(form_of(ctx, f), [&](auto last) {
+            if (buf) launch(k_gather_dump<NB, kFormBuffer, last.value>);
+            else launch(k_gather_dump<NB, kFormGlobal, last.value>);
+        });
     }
 }
 
@@ -2203,15 +2396,13 @@ constexpr int kNoAllocMaxCUs = 320;
 constexpr size_t kNoAllocPartials = 256;
 constexpr size_t kNoAllocScratchBytes =
     kNoAllocPartials + sizeof(double) * (size_t)kNoAllocMaxCUs * kRmseWavesPerCU;
-constexpr int kNoAllocMaxDevices = 64;
-
 struct NoAllocDevice {
     std::once_flag once;
     int rc = ALS_ERR_DEVICE;
     unsigned char* ptr = nullptr;   // this device's copy of the scratch array
     int cus = 0;
 };
-NoAllocDevice g_noalloc[kNoAllocMaxDevices];
+NoAllocDevice g_noalloc[kMaxDevices];
 
 }  // namespace
 
@@ -2222,7 +2413,7 @@ namespace {
 // Once per device, with that device current: its compute units and the device address of its
 // copy of `scratch`.  Called by als_init and by the first als_rmse_noalloc on a device.
 int noalloc_setup(int device) {
-    if (device < 0 || device >= kNoAllocMaxDevices) return ALS_ERR_DEVICE;
+    if (device < 0 || device >= kMaxDevices) return ALS_ERR_DEVICE;
     NoAllocDevice& d = g_noalloc[device];
     std::call_once(d.once, [&d, device]() {
         int n = 0;
@@ -2301,7 +2492,7 @@ extern "C" {
 
 size_t als_workspace_bytes(int device, int32_t f_max) {
     if (f_max < 1 || f_max > ALS_F_MAX) return 0;
-    int cus = 0, w_cap = 0, waves[kMaxNB + 1] = {0};
+    int cus = 0, w_cap = 0, waves[kMaxNB + 1][kLastForms] = {{0}};
     if (query_device(device, f_max, &cus, waves, &w_cap) != ALS_OK) return 0;
     return make_layout(waves, nb_of(f_max), cus).total;
 }
@@ -2331,7 +2522,7 @@ int als_init(als_ctx** out, int device, void* workspace, size_t workspace_bytes,
         const char* pe = getenv("ALS_PART_ENTRIES");
         if (pe && atoll(pe) > 0) part = atoll(pe);
         int groups = 1;
-        while ((int64_t)kEntriesPerGroup * groups * 2 <= part && groups < (1 << 24)) groups *= 2;
+        while ((int64_t)kGroupEntries * groups * 2 <= part && groups < (1 << 24)) groups *= 2;
         ctx->part_groups = groups;
     }
     ctx->nb_max = nb_of(f_max);
@@ -2341,7 +2532,7 @@ int als_init(als_ctx** out, int device, void* workspace, size_t workspace_bytes,
         for (int nb = 1; nb <= ctx->nb_max; ++nb) {
             int w = 0;
             if (staged_waves_for_nb(nb, ctx->cus, &w) != 0) { delete ctx; return ALS_ERR_HIP; }
-            if (w < ctx->waves[nb]) ctx->waves[nb] = w;
+            if (w < ctx->waves[nb][kLastTiles]) ctx->waves[nb][kLastTiles] = w;
         }
     }
     ctx->lay = make_layout(ctx->waves, ctx->nb_max, ctx->cus);
@@ -2432,7 +2623,7 @@ int als_half_sweep(als_ctx* ctx, const int64_t* rowptr, const int32_t* colidx, c
     }
     if (ctx->staged_gather && !staged_supported(n, f)) return ALS_ERR_UNSUPPORTED_F;
     const int nb = nb_of(f);
-    const int W = ctx->waves[nb];
+    const int W = ctx->waves[nb][form_of(ctx, f)];
     DeviceGuard guard(ctx->device);
     if (!guard.ok) return ALS_ERR_DEVICE;
     hipStream_t st = (hipStream_t)stream;
@@ -2508,7 +2699,7 @@ int als_plan(als_ctx* ctx, const int64_t* rowptr, int64_t m, int32_t f, int64_t*
     if (!ctx || !rowptr || !bounds_out || !params_out || m < 0) return ALS_ERR_INVALID_ARG;
     if (f < 1 || f > ctx->f_max) return ALS_ERR_UNSUPPORTED_F;
     if (!aligned(rowptr, 8) || !aligned(bounds_out, 8)) return ALS_ERR_ALIGN;
-    const int W = ctx->waves[nb_of(f)];
+    const int W = ctx->waves[nb_of(f)][form_of(ctx, f)];
     const int C = chunks_of(W);
     params_out[0] = C;
     params_out[1] = kCostPerEntry;
