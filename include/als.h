@@ -207,9 +207,11 @@ int als_profile_end(als_ctx* ctx, float* ms_out, int32_t capacity, int32_t* coun
  *                          each entry, column by column
  * colidx, vals, rowidx and vals_t must not be null when m > 0 and n > 0 (ALS_ERR_INVALID_ARG).
  * Outputs must not overlap the inputs.  Scratch is the context's workspace (past its status
- * block): it holds one int32 counter per column for each of R row blocks, with R chosen to fit
- * (at most 8 per compute unit, at least 1); if even one block does not fit (about 4 n bytes),
- * ALS_ERR_WORKSPACE.  Entries with a column outside [0, n) are skipped (not validated otherwise;
+ * block).  Where it holds the entries once (10 bytes each up to 65,536 columns, 12 up to 2^24, none
+ * up to 256, beside about 2.3 MB), they are sorted by column there; else it holds one int32 counter
+ * per column for each of R row blocks, with R chosen to fit (at most 8 per compute unit, at least
+ * 1), and the entries are placed from the counts.  If not even one block of counters fits (about
+ * 4 n bytes), ALS_ERR_WORKSPACE.  The result does not depend on the way taken.  Entries with a column outside [0, n) are skipped (not validated otherwise;
  * colptr[n] then counts only the others).  Queued on `stream`; it shares the workspace with the
  * other calls of the context, so it must not overlap them in time.
  */

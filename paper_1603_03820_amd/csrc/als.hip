@@ -1781,7 +1781,12 @@ __device__ __forceinline__ int64_t tr_row_begin(const int64_t* __restrict__ rowp
     return lo;
 }
 
-__global__ __launch_bounds__(256) void k_tr_zero(int32_t* __restrict__ p, int64_t count) {
+// The counting passes run when the sort (k_rx_*, below) does not: when there are more entries than
+// `over`, the most that it takes.
+__global__ __launch_bounds__(256) void k_tr_zero(const int64_t* __restrict__ rowptr, int64_t m,
+                                                 int64_t over, int32_t* __restrict__ p,
+                                                 int64_t count) {
+    if (rowptr[m] <= over) return;
     for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < count;
          i += (int64_t)gridDim.x * 256)
         p[i] = 0;
@@ -1791,7 +1796,9 @@ __global__ __launch_bounds__(256) void k_tr_zero(int32_t* __restrict__ p, int64_
 // increments does not matter).
 __global__ __launch_bounds__(256) void k_tr_count(const int64_t* __restrict__ rowptr,
                                                   const int32_t* __restrict__ colidx, int64_t m,
-                                                  int64_t n, int R, int32_t* __restrict__ cnt) {
+                                                  int64_t n, int64_t over, int R,
+                                                  int32_t* __restrict__ cnt) {
+    if (rowptr[m] <= over) return;
     const int b = blockIdx.x;
     const int64_t k0 = rowptr[tr_row_begin(rowptr, m, R, b)];
     const int64_t k1 = rowptr[tr_row_begin(rowptr, m, R, b + 1)];
@@ -1804,8 +1811,11 @@ __global__ __launch_bounds__(256) void k_tr_count(const int64_t* __restrict__ ro
 
 // Per column v (one thread each): cnt[b][v] <- the sum over b' < b, and colptr[v] <- the
 // column's total (scanned over v afterwards).
-__global__ __launch_bounds__(256) void k_tr_colscan(int64_t n, int R, int32_t* __restrict__ cnt,
+__global__ __launch_bounds__(256) void k_tr_colscan(const int64_t* __restrict__ rowptr, int64_t m,
+                                                    int64_t n, int64_t over, int R,
+                                                    int32_t* __restrict__ cnt,
                                                     int64_t* __restrict__ colptr) {
+    if (rowptr[m] <= over) return;
     const int64_t v = (int64_t)blockIdx.x * 256 + threadIdx.x;
     if (v >= n) return;
     int32_t run = 0;
@@ -1891,6 +1901,13 @@ __global__ __launch_bounds__(256) void k_scan_apply(int64_t* __restrict__ a, int
     }
 }
 
+// LDS atomics whose result is not used may still be on their way at a barrier (the compiler leaves
+// their wait out where they end a loop body, and counts of other waves were lost that way): waits
+// for this wave's before it meets the others.
+__device__ __forceinline__ void lds_atomics_done() {
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+}
+
 // LDS forms of the count and the scatter, for n <= kTrLdsCols: the block's per-column counters
 // (cursors) live in the workgroup's LDS.  Counting: one workgroup of 256 per row block adds its
 // entries into LDS and writes the n counts out.  Scatter: one wave per row block loads
@@ -1900,8 +1917,9 @@ constexpr int kTrLdsCols = 40960;   // 160 KB of int32 counters
 
 __global__ __launch_bounds__(256) void k_tr_count_lds(const int64_t* __restrict__ rowptr,
                                                       const int32_t* __restrict__ colidx,
-                                                      int64_t m, int n, int R,
+                                                      int64_t m, int n, int64_t over, int R,
                                                       int32_t* __restrict__ cnt) {
+    if (rowptr[m] <= over) return;
     extern __shared__ int32_t lcnt[];
     const int b = blockIdx.x;
     for (int v = threadIdx.x; v < n; v += 256) lcnt[v] = 0;
@@ -1912,6 +1930,7 @@ __global__ __launch_bounds__(256) void k_tr_count_lds(const int64_t* __restrict_
         const int32_t v = colidx[k];
         if (v >= 0 && v < n) atomicAdd(&lcnt[v], 1);
     }
+    lds_atomics_done();
     __syncthreads();
     int32_t* row = cnt + (size_t)b * (size_t)n;
     for (int v = threadIdx.x; v < n; v += 256) row[v] = lcnt[v];
@@ -1919,9 +1938,10 @@ __global__ __launch_bounds__(256) void k_tr_count_lds(const int64_t* __restrict_
 
 __global__ __launch_bounds__(kWave) void k_tr_scatter_lds(
     const int64_t* __restrict__ rowptr, const int32_t* __restrict__ colidx,
-    const float* __restrict__ vals, int64_t m, int n, int R, const int32_t* __restrict__ cnt,
-    const int64_t* __restrict__ colptr, int32_t* __restrict__ rowidx,
-    float* __restrict__ vals_t) {
+    const float* __restrict__ vals, int64_t m, int n, int64_t over, int R,
+    const int32_t* __restrict__ cnt, const int64_t* __restrict__ colptr,
+    int32_t* __restrict__ rowidx, float* __restrict__ vals_t) {
+    if (rowptr[m] <= over) return;
     // cur[v]: where this block's next entry of column v goes -- its absolute position when
     // nnz < 2^31 (then no colptr read per entry), else its position within column v's run
     extern __shared__ int32_t cur[];
@@ -1983,9 +2003,10 @@ __global__ __launch_bounds__(kWave) void k_tr_scatter_lds(
 // a counter; the fence after each row orders its counter updates before the next row's.
 __global__ __launch_bounds__(kWave) void k_tr_scatter(
     const int64_t* __restrict__ rowptr, const int32_t* __restrict__ colidx,
-    const float* __restrict__ vals, int64_t m, int64_t n, int R, int32_t* __restrict__ cnt,
-    const int64_t* __restrict__ colptr, int32_t* __restrict__ rowidx,
+    const float* __restrict__ vals, int64_t m, int64_t n, int64_t over, int R,
+    int32_t* __restrict__ cnt, const int64_t* __restrict__ colptr, int32_t* __restrict__ rowidx,
     float* __restrict__ vals_t) {
+    if (rowptr[m] <= over) return;
     const int b = blockIdx.x, lane = threadIdx.x;
     const int64_t u0 = tr_row_begin(rowptr, m, R, b), u1 = tr_row_begin(rowptr, m, R, b + 1);
     int32_t* row = cnt + (size_t)b * (size_t)n;
@@ -2001,6 +2022,359 @@ __global__ __launch_bounds__(kWave) void k_tr_scatter(
             }
         }
         __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "workgroup");
+    }
+}
+
+// ---- the transpose as a stable radix sort by column (nnz up to what the workspace holds)
+//
+// What bounds the passes above is their scattered 4-byte stores: a row block's entries fall into n
+// column runs of a few entries, every store leaves L2 as a partial-line write of its own, and 100M
+// ratings x 17,770 columns take 5.6 ms for 0.8 GB of output.  So, where the workspace can hold the
+// entries once (rx_layout), they are sorted by column digit, at most 8 bits a pass, lowest first: two
+// passes for n <= 65,536, three up to 2^24 columns, one for n <= 256.  The bits are dealt evenly, the
+// first pass getting the fewest: its digits are the most evenly spread, so its runs are the shortest
+// (a tile's entries over its digits).  A pass cuts the entries into
+// kRxBlocks equal ranges, counts digits per range (k_rx_count), makes the counts offsets
+// (k_rx_offsets) and moves the entries (k_rx_move): tiles of 4,096 entries are ranked by digit
+// (stable: a wave ranks 64 consecutive entries by ballots), put in order in LDS and written out in
+// runs of at least 16 entries per digit on average.  From the second pass on, k_rx_count also counts every
+// combination of the digit with the lower ones, the last of them being the columns' counts: the
+// entries are already sorted by the lower digits, so it counts one lower value's stretch at a time
+// in LDS and adds it to the global counts once.
+// Movie matrix: 6.4 -> 2.0 ms for the whole transpose; 250,000 x 625,000 with 62.5M ratings, whose
+// counters do not fit in LDS: 9.5 -> 1.8 ms.  (8 bits in the first pass: 2.06 and 2.04 ms; 768 blocks
+// instead of 1,536: 2.44 and 2.32 ms.)
+constexpr int kRxThreads = 256;
+constexpr int kRxWaves = kRxThreads / kWave;
+constexpr int kRxPer = 16;                                // entries per thread and tile
+constexpr int kRxTile = kRxThreads * kRxPer;
+constexpr int kRxDigits = 256;
+constexpr int kRxBlocks = 1536;   // twice what is resident (three blocks of 53 KB of LDS per CU)
+constexpr int64_t kRxMaxCols = 1 << 24;
+
+// The entries of a pass.  From the CSR (key null): colidx, vals and the row of each position;
+// between passes: row, value and the column bits above the digits already sorted by.
+struct RxSrc {
+    const int64_t* rowptr;
+    int64_t m;
+    const int32_t* colidx;   // first pass
+    const float* vals;
+    const uint32_t* row;     // later passes
+    const float* val;
+    const uint16_t* key;
+};
+
+// Sum of the counts before and the sum of all of counts[0, 256), one per thread.
+__device__ __forceinline__ int rx_scan256(int x, int* sh, int* total) {
+    const int t = threadIdx.x, lane = t & 63, w = t >> 6;
+    int inc = x;
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+        const int y = __shfl_up(inc, o);
+        if (lane >= o) inc += y;
+    }
+    if (lane == 63) sh[w] = inc;
+    __syncthreads();
+    int base = 0;
+    for (int i = 0; i < w; ++i) base += sh[i];
+    *total = sh[0] + sh[1] + sh[2] + sh[3];
+    __syncthreads();
+    return base + inc - x;
+}
+
+// Entries [lo, hi) of block b's range of `count` entries.
+__device__ __forceinline__ void rx_range(int count, int b, int& lo, int& hi) {
+    lo = (int)((int64_t)count * b / kRxBlocks);
+    hi = (int)((int64_t)count * (b + 1) / kRxBlocks);
+}
+
+// First pass: digit counts of the CSR's ranges (columns outside [0, n) left out), hist[d][b].
+__global__ __launch_bounds__(kRxThreads) void k_rx_count_first(
+    const int64_t* __restrict__ rowptr, const int32_t* __restrict__ colidx, int64_t m, int n,
+    int64_t cap, int width, int* __restrict__ hist) {
+    if (rowptr[m] > cap) return;
+    __shared__ int h[kRxDigits];
+    const int mask = (1 << width) - 1;   // a digit of `width` bits
+    const int t = threadIdx.x, b = blockIdx.x;
+    h[t] = 0;
+    __syncthreads();
+    int lo, hi;
+    rx_range((int)rowptr[m], b, lo, hi);
+    for (int k0 = lo; k0 < hi; k0 += 4 * kRxThreads) {
+        int v[4];
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            const int k = k0 + j * kRxThreads + t;
+            v[j] = k < hi ? colidx[k] : -1;
+        }
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+            if (v[j] >= 0 && v[j] < n) atomicAdd(&h[v[j] & mask], 1);
+    }
+    lds_atomics_done();
+    __syncthreads();
+    hist[t * kRxBlocks + b] = h[t];
+}
+
+// Later passes: digit counts of the ranges, and counts[digit << bits | lower] for every lower
+// value, whose entries are [starts[lower], starts[lower + 1]).  OUT is int (the starts' counts of
+// the next pass) or unsigned long long (the columns' counts, in colptr).
+template <class OUT>
+__global__ __launch_bounds__(kRxThreads) void k_rx_count(const int64_t* __restrict__ rowptr,
+                                                         int64_t m, int64_t cap,
+                                                         const uint16_t* __restrict__ key,
+                                                         const int* __restrict__ starts, int bits,
+                                                         int width, int64_t limit,
+                                                         int* __restrict__ hist,
+                                                         OUT* __restrict__ counts) {
+    if (rowptr[m] > cap) return;
+    __shared__ int h[kRxDigits];
+    const int t = threadIdx.x, b = blockIdx.x, mask = (1 << width) - 1;
+    int lo, hi;
+    rx_range(starts[1 << bits], b, lo, hi);
+    // the last lower value from `low` on that starts at or before entry k: the one that holds it
+    const auto holder = [&](int low, int k) {
+        int top = (1 << bits) - 1;
+        while (low < top) {
+            const int mid = (low + top + 1) >> 1;
+            if (starts[mid] <= k) low = mid; else top = mid - 1;
+        }
+        return low;
+    };
+    int all = 0, low = holder(0, lo);
+    h[t] = 0;
+    __syncthreads();
+    for (int k = lo; k < hi; ++low) {
+        if (starts[low + 1] <= k) low = holder(low, k);   // past lower values without entries
+        const int next = starts[low + 1], end = next < hi ? next : hi;
+        for (int k0 = k; k0 < end; k0 += 4 * kRxThreads) {
+            int v[4];
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                const int i = k0 + j * kRxThreads + t;
+                v[j] = i < end ? (int)key[i] : -1;
+            }
+#pragma unroll
+            for (int j = 0; j < 4; ++j)
+                if (v[j] >= 0) atomicAdd(&h[v[j] & mask], 1);
+        }
+        lds_atomics_done();
+        __syncthreads();
+        const int c = h[t];
+        h[t] = 0;
+        all += c;
+        const int64_t at = ((int64_t)t << bits) | low;
+        if (c && at < limit) atomicAdd(&counts[at], (OUT)c);
+        __syncthreads();
+        k = end;
+    }
+    hist[t * kRxBlocks + b] = all;
+}
+
+// Per digit: its ranges' counts -> offsets within the digit, and the digit's total (after the
+// first pass also colptr[d] when the digit is the whole column).
+__global__ __launch_bounds__(kRxThreads) void k_rx_offsets(const int64_t* __restrict__ rowptr,
+                                                           int64_t m, int64_t cap,
+                                                           int* __restrict__ hist,
+                                                           int* __restrict__ totals,
+                                                           int64_t* __restrict__ colptr, int n) {
+    if (rowptr[m] > cap) return;
+    __shared__ int sh[kRxWaves];
+    const int d = blockIdx.x, t = threadIdx.x;
+    constexpr int kPer = kRxBlocks / kRxThreads;
+    int* h = hist + d * kRxBlocks + t * kPer;
+    int v[kPer], sum = 0, total;
+#pragma unroll
+    for (int j = 0; j < kPer; ++j) {
+        v[j] = h[j];
+        sum += v[j];
+    }
+    int run = rx_scan256(sum, sh, &total);
+#pragma unroll
+    for (int j = 0; j < kPer; ++j) {
+        h[j] = run;
+        run += v[j];
+    }
+    if (t == 0) {
+        totals[d] = total;
+        if (colptr && d < n) colptr[d] = total;
+    }
+}
+
+// starts[0, 2^bits] from counts (one workgroup).
+__global__ __launch_bounds__(kRxThreads) void k_rx_starts(const int64_t* __restrict__ rowptr,
+                                                          int64_t m, int64_t cap,
+                                                          const int* __restrict__ counts, int bits,
+                                                          int* __restrict__ starts) {
+    if (rowptr[m] > cap) return;
+    __shared__ int sh[kRxWaves];
+    const int t = threadIdx.x, size = 1 << bits;
+    int carry = 0;
+    for (int base = 0; base < size; base += kRxThreads * 16) {
+        int v[16], sum = 0, total;
+#pragma unroll
+        for (int j = 0; j < 16; ++j) {
+            const int i = base + t * 16 + j;
+            v[j] = i < size ? counts[i] : 0;
+            sum += v[j];
+        }
+        int run = carry + rx_scan256(sum, sh, &total);
+#pragma unroll
+        for (int j = 0; j < 16; ++j) {
+            const int i = base + t * 16 + j;
+            if (i < size) starts[i] = run;
+            run += v[j];
+        }
+        carry += total;
+    }
+    if (t == 0) starts[size] = carry;
+}
+
+// Move a pass's entries to their places.  FIRST: from the CSR.  LAST: no key is written.
+template <bool FIRST, bool LAST>
+__global__ __launch_bounds__(kRxThreads) __attribute__((amdgpu_waves_per_eu(3))) void k_rx_move(RxSrc in, int n, int64_t cap, int width,
+                                                        const int* __restrict__ hist,
+                                                        const int* __restrict__ totals,
+                                                        uint32_t* __restrict__ row_out,
+                                                        float* __restrict__ val_out,
+                                                        uint16_t* __restrict__ key_out) {
+    if (in.rowptr[in.m] > cap) return;
+    __shared__ uint32_t srow[kRxTile];
+    __shared__ float sval[kRxTile];
+    __shared__ uint32_t skey[kRxTile];   // first the row marks of the tile, then the keys in order
+    __shared__ int wcnt[kRxWaves][kRxDigits];   // counts, then places in the tile's order
+    __shared__ int shift[kRxDigits];            // from a place in the tile's order to the output
+    __shared__ int sh[kRxWaves];
+    const int t = threadIdx.x, lane = t & 63, w = t >> 6, b = blockIdx.x;
+    const uint32_t mask = (1u << width) - 1;
+    int count;
+    // where this block's next entry of digit t goes
+    int dest = rx_scan256(totals[t], sh, &count) + hist[t * kRxBlocks + b];
+    if (FIRST) count = (int)in.rowptr[in.m];
+    int lo, hi;
+    rx_range(count, b, lo, hi);
+    int64_t u = 0;   // FIRST: row of the tile's first entry
+    if (FIRST && lo < hi) {
+        int64_t a = 0, z = in.m - 1;   // largest row that starts at or before lo
+        while (a < z) {
+            const int64_t mid = (a + z + 1) >> 1;
+            if (in.rowptr[mid] <= lo) a = mid; else z = mid - 1;
+        }
+        u = a;
+    }
+    for (int t0 = lo; t0 < hi; t0 += kRxTile) {
+        const int t1 = t0 + kRxTile < hi ? t0 + kRxTile : hi;
+        const int wbase = t0 + w * kRxPer * kWave;   // this wave's entries of the tile
+        uint32_t key[kRxPer], row[kRxPer];
+        float val[kRxPer];
+#pragma unroll
+        for (int j = 0; j < kRxPer; ++j) {
+            const int k = wbase + j * kWave + lane;
+            key[j] = 0xFFFFFFFFu;   // not an entry
+            if (k < t1) {
+                if (FIRST) {
+                    const int c = in.colidx[k];
+                    if (c >= 0 && c < n) key[j] = (uint32_t)c;
+                    val[j] = in.vals[k];
+                } else {
+                    key[j] = in.key[k];
+                    val[j] = in.val[k];
+                    row[j] = in.row[k];
+                }
+            }
+        }
+#pragma unroll
+        for (int i = 0; i < kRxWaves; ++i) wcnt[i][t] = 0;
+        if (FIRST) {
+            // mark where rows start in the tile (the last one of several that start together), by
+            // their distance from u; the last mark at or before an entry is its row
+#pragma unroll
+            for (int j = 0; j < kRxPer; ++j) skey[j * kRxThreads + t] = 0;
+            __syncthreads();
+            int64_t passed = 0;   // rows after u that start before t1
+            for (int64_t r0 = u + 1;; r0 += kRxThreads) {
+                const int64_t r = r0 + t;
+                const int64_t at = r < in.m ? in.rowptr[r] : (int64_t)t1;
+                const bool inside = at < t1;
+                if (inside) atomicMax(&skey[at - t0], (uint32_t)(r - u));
+                lds_atomics_done();
+                const int c = __syncthreads_count(inside);
+                passed += c;
+                if (c < kRxThreads) break;
+            }
+            uint32_t last = 0;   // the wave's last mark so far (marks grow with their place)
+#pragma unroll
+            for (int j = 0; j < kRxPer; ++j) {
+                const uint32_t x = skey[w * kRxPer * kWave + j * kWave + lane];
+                const uint64_t marks = __ballot(x != 0);
+                const uint64_t upto = marks & (~0ull >> (63 - lane));
+                const uint32_t own = (uint32_t)__shfl((int)x, upto ? 63 - __builtin_clzll(upto) : 0);
+                row[j] = upto ? own : last;
+                if (marks)
+                    last = (uint32_t)__builtin_amdgcn_readlane((int)x, 63 - __builtin_clzll(marks));
+            }
+            if (lane == 0) sh[w] = (int)last;
+            __syncthreads();
+            uint32_t before = 0;   // the earlier waves' last mark
+            for (int i = 0; i < w; ++i) before = max(before, (uint32_t)sh[i]);
+#pragma unroll
+            for (int j = 0; j < kRxPer; ++j) row[j] = (uint32_t)u + max(row[j], before);
+            u += passed;
+        }
+        __syncthreads();
+        // rank by digit within the wave's entries
+        int rank[kRxPer];
+#pragma unroll
+        for (int j = 0; j < kRxPer; ++j) {
+            const bool live = key[j] != 0xFFFFFFFFu;
+            const uint32_t d = key[j] & mask;
+            uint64_t same = __ballot(live);
+#pragma unroll
+            for (int bit = 0; bit < 8; ++bit) {
+                const uint64_t has = __ballot((d >> bit) & 1);
+                same &= ((d >> bit) & 1) ? has : ~has;
+            }
+            const int before = __popcll(same & ((1ull << lane) - 1));
+            int old = 0;
+            if (live && before == 0) old = atomicAdd(&wcnt[w][d], __popcll(same));
+            rank[j] = before + __shfl(old, live ? __builtin_ctzll(same) : lane);
+        }
+        lds_atomics_done();
+        __syncthreads();
+        int c[kRxWaves], sum = 0, tile;   // thread t: digit t
+#pragma unroll
+        for (int i = 0; i < kRxWaves; ++i) {
+            c[i] = wcnt[i][t];
+            sum += c[i];
+        }
+        int place = rx_scan256(sum, sh, &tile);
+        shift[t] = dest - place;
+        dest += sum;
+#pragma unroll
+        for (int i = 0; i < kRxWaves; ++i) {
+            wcnt[i][t] = place;
+            place += c[i];
+        }
+        __syncthreads();
+#pragma unroll
+        for (int j = 0; j < kRxPer; ++j) {
+            if (key[j] != 0xFFFFFFFFu) {
+                const uint32_t d = key[j] & mask;
+                const int at = wcnt[w][d] + rank[j];
+                srow[at] = row[j];
+                sval[at] = val[j];
+                skey[at] = key[j];
+            }
+        }
+        __syncthreads();
+        for (int i = t; i < tile; i += kRxThreads) {
+            const uint32_t k = skey[i];
+            const int to = i + shift[k & mask];
+            row_out[to] = srow[i];
+            val_out[to] = sval[i];
+            if (!LAST) key_out[to] = (uint16_t)(k >> width);
+        }
+        __syncthreads();
     }
 }
 
@@ -2478,6 +2852,100 @@ hipError_t rmse_launch(int cus, int cap_per_cu, bool force_global, hipStream_t s
     return hipGetLastError();
 }
 
+// The radix transpose's share of the workspace.
+struct RxSpace {
+    int passes;            // 1..3
+    int width[3];          // bits of each pass's digit
+    int *hist, *totals, *counts, *starts;
+    uint32_t* row;         // entries between passes
+    float* val;
+    uint16_t *key, *key2;  // key2: after the first of three passes (row and value in the outputs)
+};
+
+// Lay it out in `bytes` at p (256-byte aligned); returns how many entries it holds (0: the sort
+// cannot run).
+int64_t rx_layout(unsigned char* p, size_t bytes, int64_t n, RxSpace* rx) {
+    if (n > kRxMaxCols) return 0;
+    int bits = 1;
+    while (((int64_t)1 << bits) < n) ++bits;
+    rx->passes = (bits + 7) / 8;
+    for (int i = 0; i < rx->passes; ++i)
+        rx->width[i] = bits / rx->passes + (i >= rx->passes - bits % rx->passes ? 1 : 0);
+    size_t off = 0;
+    const auto take = [&](size_t b) {
+        unsigned char* at = p + off;
+        off = align256(off + b);
+        return at;
+    };
+    rx->hist = (int*)take(sizeof(int) * kRxDigits * kRxBlocks);
+    rx->totals = (int*)take(sizeof(int) * kRxDigits);
+    rx->counts = (int*)take(sizeof(int) << 16);
+    rx->starts = (int*)take(sizeof(int) * ((1 << 16) + 1));
+    if (rx->passes == 1) return off <= bytes ? INT32_MAX / 2 : 0;
+    const size_t each = sizeof(uint32_t) + sizeof(float) +
+                        (rx->passes - 1) * sizeof(uint16_t);
+    const size_t slack = 4 * 256;   // alignment of the arrays below
+    if (bytes < off + slack + each) return 0;
+    int64_t cap = (int64_t)((bytes - off - slack) / each);
+    if (cap > INT32_MAX / 2) cap = INT32_MAX / 2;
+    rx->row = (uint32_t*)take(sizeof(uint32_t) * (size_t)cap);
+    rx->val = (float*)take(sizeof(float) * (size_t)cap);
+    rx->key = (uint16_t*)take(sizeof(uint16_t) * (size_t)cap);
+    rx->key2 = (uint16_t*)take(rx->passes == 3 ? sizeof(uint16_t) * (size_t)cap : 0);
+    return cap;
+}
+
+// The passes (see k_rx_count_first); colptr is zeroed and left with the columns' counts.
+void rx_launch(const RxSpace& rx, int64_t cap, hipStream_t st, const int64_t* rowptr,
+               const int32_t* colidx, const float* vals, int64_t m, int64_t n, int64_t* colptr,
+               uint32_t* rowidx, float* vals_t) {
+    const dim3 grid(kRxBlocks), block(kRxThreads), digits(kRxDigits);
+    auto* columns = (unsigned long long*)colptr;
+    const RxSrc csr{rowptr, m, colidx, vals, nullptr, nullptr, nullptr};
+    const RxSrc out{rowptr, m, nullptr, nullptr, rowidx, vals_t, rx.key2};
+    const RxSrc mid{rowptr, m, nullptr, nullptr, rx.row, rx.val, rx.key};
+    const int w0 = rx.width[0], w1 = rx.width[1], w2 = rx.width[2];
+    hipLaunchKernelGGL(k_rx_count_first, grid, block, 0, st, rowptr, colidx, m, (int)n, cap, w0,
+                       rx.hist);
+    hipLaunchKernelGGL(k_rx_offsets, digits, block, 0, st, rowptr, m, cap, rx.hist, rx.totals,
+                       rx.passes == 1 ? colptr : nullptr, (int)n);
+    if (rx.passes == 1) {
+        hipLaunchKernelGGL((k_rx_move<true, true>), grid, block, 0, st, csr, (int)n, cap, w0,
+                           rx.hist, rx.totals, rowidx, vals_t, nullptr);
+        return;
+    }
+    hipLaunchKernelGGL(k_rx_starts, dim3(1), block, 0, st, rowptr, m, cap, rx.totals, w0,
+                       rx.starts);
+    int last = w1;
+    if (rx.passes == 2) {
+        hipLaunchKernelGGL((k_rx_move<true, false>), grid, block, 0, st, csr, (int)n, cap, w0,
+                           rx.hist, rx.totals, rx.row, rx.val, rx.key);
+        hipLaunchKernelGGL(k_rx_count<unsigned long long>, grid, block, 0, st, rowptr, m, cap,
+                           rx.key, rx.starts, w0, w1, n, rx.hist, columns);
+    } else {
+        const int64_t cells = (int64_t)1 << (w0 + w1);
+        hipLaunchKernelGGL((k_rx_move<true, false>), grid, block, 0, st, csr, (int)n, cap, w0,
+                           rx.hist, rx.totals, rowidx, vals_t, rx.key2);
+        hipLaunchKernelGGL(k_tr_zero, dim3(256), dim3(256), 0, st, rowptr, m, (int64_t)-1,
+                           rx.counts, cells);
+        hipLaunchKernelGGL(k_rx_count<int>, grid, block, 0, st, rowptr, m, cap, rx.key2, rx.starts,
+                           w0, w1, cells, rx.hist, rx.counts);
+        hipLaunchKernelGGL(k_rx_offsets, digits, block, 0, st, rowptr, m, cap, rx.hist, rx.totals,
+                           nullptr, 0);
+        hipLaunchKernelGGL(k_rx_starts, dim3(1), block, 0, st, rowptr, m, cap, rx.counts, w0 + w1,
+                           rx.starts);
+        hipLaunchKernelGGL((k_rx_move<false, false>), grid, block, 0, st, out, (int)n, cap, w1,
+                           rx.hist, rx.totals, rx.row, rx.val, rx.key);
+        hipLaunchKernelGGL(k_rx_count<unsigned long long>, grid, block, 0, st, rowptr, m, cap,
+                           rx.key, rx.starts, w0 + w1, w2, n, rx.hist, columns);
+        last = w2;
+    }
+    hipLaunchKernelGGL(k_rx_offsets, digits, block, 0, st, rowptr, m, cap, rx.hist, rx.totals,
+                       nullptr, 0);
+    hipLaunchKernelGGL((k_rx_move<false, true>), grid, block, 0, st, mid, (int)n, cap, last,
+                       rx.hist, rx.totals, rowidx, vals_t, nullptr);
+}
+
 void profile_free(als_ctx* ctx) {
     if (!ctx->prof_ev) return;
     for (int i = 0; i < 4 * ctx->prof_cap; ++i) (void)hipEventDestroy(ctx->prof_ev[i]);
@@ -2738,51 +3206,62 @@ int als_csr_to_csc(als_ctx* ctx, const int64_t* rowptr, const int32_t* colidx, c
     DeviceGuard guard(ctx->device);
     if (!guard.ok) return ALS_ERR_DEVICE;
     hipStream_t st = (hipStream_t)stream;
-    int64_t* sums = (int64_t*)(ctx->ws + ctx->lay.bounds);
-    int32_t* cnt = (int32_t*)(ctx->ws + ctx->lay.bounds + sums_bytes);
-    const int64_t cells = R * n;
-    if (cells > 0) {
-        const int64_t zb = (cells + 255) / 256;
-        hipLaunchKernelGGL(k_tr_zero, dim3((unsigned)(zb < 65536 ? zb : 65536)), dim3(256), 0, st,
-                           cnt, cells);
-    }
-    // LDS counters when one row block's fit in a workgroup's LDS
+    unsigned char* base = ctx->ws + ctx->lay.bounds;
+    int64_t* sums = (int64_t*)base;
+    int32_t* cnt = (int32_t*)(base + sums_bytes);
+    // The sort runs when the entries fit beside its counters, the counting passes otherwise.  The
+    // number of entries is known on the device only: both are launched, unless no m x n matrix has
+    // too many, and the one that does not run returns at once.
+    RxSpace rx;
+    const int64_t cap =
+        m > 0 && n > 0 ? rx_layout(base + sums_bytes, avail - sums_bytes, n, &rx) : 0;
+    const bool counting = m > 0 && n > 0 && (m > cap || n > cap || m * n > cap);
     const size_t lds_bytes = sizeof(int32_t) * (size_t)(n > 0 ? n : 1);
-    bool lds = n <= kTrLdsCols && lds_bytes <= ctx->lds_per_block;
-    if (lds && m > 0 && n > 0) {
-        hipError_t ea = hipFuncSetAttribute((const void*)k_tr_count_lds,
-                                            hipFuncAttributeMaxDynamicSharedMemorySize,
-                                            (int)lds_bytes);
-        if (ea == hipSuccess)
-            ea = hipFuncSetAttribute((const void*)k_tr_scatter_lds,
-                                     hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_bytes);
-        if (ea != hipSuccess) return fail_hip(ctx, ea);
+    const bool lds = n <= kTrLdsCols && lds_bytes <= ctx->lds_per_block;
+    if (n > 0) {   // colptr: the columns' counts (of the sort), then their scan
+        const int64_t words = 2 * n, zb = (words + 255) / 256;
+        hipLaunchKernelGGL(k_tr_zero, dim3((unsigned)(zb < 4096 ? zb : 4096)), dim3(256), 0, st,
+                           rowptr, m, (int64_t)-1, (int32_t*)colptr, words);
     }
-    if (m > 0 && n > 0) {
+    if (cap > 0)
+        rx_launch(rx, cap, st, rowptr, colidx, vals, m, n, colptr, (uint32_t*)rowidx, vals_t);
+    if (counting) {
+        // LDS counters when one row block's fit in a workgroup's LDS
+        if (lds) {
+            hipError_t ea = hipFuncSetAttribute((const void*)k_tr_count_lds,
+                                                hipFuncAttributeMaxDynamicSharedMemorySize,
+                                                (int)lds_bytes);
+            if (ea == hipSuccess)
+                ea = hipFuncSetAttribute((const void*)k_tr_scatter_lds,
+                                         hipFuncAttributeMaxDynamicSharedMemorySize,
+                                         (int)lds_bytes);
+            if (ea != hipSuccess) return fail_hip(ctx, ea);
+        }
+        const int64_t cells = R * n, zb = (cells + 255) / 256;
+        hipLaunchKernelGGL(k_tr_zero, dim3((unsigned)(zb < 4096 ? zb : 4096)), dim3(256), 0, st,
+                           rowptr, m, cap, cnt, cells);
         if (lds)
-            hipLaunchKernelGGL(k_tr_count_lds, dim3((unsigned)R), dim3(256),
-                               sizeof(int32_t) * (size_t)n, st, rowptr, colidx, m, (int)n, (int)R,
-                               cnt);
+            hipLaunchKernelGGL(k_tr_count_lds, dim3((unsigned)R), dim3(256), lds_bytes, st, rowptr,
+                               colidx, m, (int)n, cap, (int)R, cnt);
         else
             hipLaunchKernelGGL(k_tr_count, dim3((unsigned)R), dim3(256), 0, st, rowptr, colidx,
-                               m, n, (int)R, cnt);
+                               m, n, cap, (int)R, cnt);
+        hipLaunchKernelGGL(k_tr_colscan, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st,
+                           rowptr, m, n, cap, (int)R, cnt, colptr);
     }
-    if (n > 0)
-        hipLaunchKernelGGL(k_tr_colscan, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, n,
-                           (int)R, cnt, colptr);
     if (n > 0)
         hipLaunchKernelGGL(k_scan_sums, dim3((unsigned)tiles), dim3(256), 0, st, colptr, n, sums);
     hipLaunchKernelGGL(k_scan_top, dim3(1), dim3(256), 0, st, sums, (int64_t)tiles, colptr, n);
     if (n > 0)
         hipLaunchKernelGGL(k_scan_apply, dim3((unsigned)tiles), dim3(256), 0, st, colptr, n, sums);
-    if (m > 0 && n > 0) {
+    if (counting) {
         if (lds)
-            hipLaunchKernelGGL(k_tr_scatter_lds, dim3((unsigned)R), dim3(kWave),
-                               sizeof(int32_t) * (size_t)n, st, rowptr, colidx, vals, m, (int)n,
-                               (int)R, cnt, colptr, rowidx, vals_t);
+            hipLaunchKernelGGL(k_tr_scatter_lds, dim3((unsigned)R), dim3(kWave), lds_bytes, st,
+                               rowptr, colidx, vals, m, (int)n, cap, (int)R, cnt, colptr, rowidx,
+                               vals_t);
         else
             hipLaunchKernelGGL(k_tr_scatter, dim3((unsigned)R), dim3(kWave), 0, st, rowptr,
-                               colidx, vals, m, n, (int)R, cnt, colptr, rowidx, vals_t);
+                               colidx, vals, m, n, cap, (int)R, cnt, colptr, rowidx, vals_t);
     }
     hipError_t e = hipGetLastError();
     return e == hipSuccess ? ALS_OK : fail_hip(ctx, e);
