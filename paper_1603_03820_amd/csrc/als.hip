@@ -1456,12 +1456,20 @@ void k_herm_solve(
 // that chunk's first piece if it started in row u, else as its last), then the piece starting at
 // each boundary b_first..b_last that cuts u, in slot 2b (empty, and unwritten, when several
 // boundaries snapped to one cut point).  The boundaries cutting one row are consecutive, so both
-// ends are found by binary search over the sorted bounds.  A row with more than kPieceGroup
-// boundary pieces is summed in two passes: every kPieceGroup-th boundary leads a group and sums
+// ends are found by search over the sorted bounds.  A long row with more than kPieceGroup
+// boundaries (sums_in_groups) is summed in two passes: every kPieceGroup-th boundary leads a group and sums
 // the group's pieces, in chunk order, into its own slot; then the row's first boundary adds the
 // first piece and the group sums, in order, and solves.  The order is fixed, so the result does
 // not depend on timing.
 constexpr int kPieceGroup = 16;
+// Rows summed in two passes: those of more than kPieceGroup boundaries and long enough for as many
+// pieces (cut points lie kSnap entries apart; a short sweep's chunks are smaller than that, and
+// hundreds of boundaries fall on a few cut points).  An iteration on 1M ratings at f = 40, both
+// reduce kernels of both sides: 78 us when every row of more than 16 boundaries took two passes and
+// boundaries were looked at one by one, 54 us now.
+__device__ __forceinline__ bool sums_in_groups(int boundaries, int64_t nu) {
+    return boundaries > kPieceGroup && nu > (int64_t)kPieceGroup * kSnap;
+}
 // Blocks of the reduce kernels.  One per boundary cost 9 us a kernel where no row is cut (tiny,
 // C = 36,864); 2,048 (all resident at f = 100) leave each wave up to nine cut rows one after the
 // other: 133 us against 95 for k_reduce_solve on the movie user side, and 296 us against 264 for a
@@ -1516,16 +1524,23 @@ __device__ __forceinline__ void cut_range(const int64_t* __restrict__ rowptr, in
     b_last = in;
 }
 
-// Add the non-empty boundary pieces of row u for boundaries bb in [from, to] into acc.
+// Add the non-empty boundary pieces of row u for boundaries bb in [from, to] into acc, in order (the
+// piece of chunk bb runs to the next boundary in the row, or to the row's end).  A wave looks at 64
+// boundaries at once: in a short sweep most of a row's boundaries fall on the same few cut points.
 template <int NB>
 __device__ __forceinline__ void add_pieces(f4 (&acc)[ntiles(NB)], const int64_t* __restrict__ bounds,
                                            const float* __restrict__ slots, int from, int to,
                                            int b_last, int64_t nu, int lane) {
-    for (int bb = from; bb <= to; ++bb) {
-        // the piece of chunk bb runs to the next boundary in the row, or to the row's end
-        const int64_t piece_end = bb < b_last ? bounds[2 * (bb + 1) + 1] : nu;
-        if (bounds[2 * bb + 1] < piece_end)
+    for (int base = from; base <= to; base += kWave) {
+        const int x = base + lane;
+        const bool some =
+            x <= to && bounds[2 * x + 1] < (x < b_last ? bounds[2 * (x + 1) + 1] : nu);
+        uint64_t todo = __ballot(some);
+        while (todo) {
+            const int bb = base + __builtin_ctzll(todo);
+            todo &= todo - 1;
             add_slot<NB>(acc, slots + (size_t)(2 * bb) * slot_floats(NB), lane);
+        }
     }
 }
 
@@ -1556,13 +1571,16 @@ __global__ __launch_bounds__(kWave) void k_reduce_groups(
     const auto pick = [&](int b) {
         if (!cuts_row(rowptr, m, bounds, b)) return false;
         const int64_t u = bounds[2 * b];
+        if (!sums_in_groups(kPieceGroup + 1, rowptr[u + 1] - rowptr[u])) return false;
         return (b > 1 && bounds[2 * (b - 1)] == u) || (b + 1 < C && bounds[2 * (b + 1)] == u);
     };
     for_boundaries(C, lane, pick, [&](int b) {
         const int64_t u = bounds[2 * b];
         int b_first, b_last;
         cut_range(rowptr, m, bounds, C, b, u, b_first, b_last);
-        if (b_last - b_first + 1 <= kPieceGroup || (b - b_first) % kPieceGroup != 0) return;
+        if (!sums_in_groups(b_last - b_first + 1, rowptr[u + 1] - rowptr[u]) ||
+            (b - b_first) % kPieceGroup != 0)
+            return;
         f4 acc[ntiles(NB)];
 #pragma unroll
         for (int t = 0; t < ntiles(NB); ++t) acc[t] = f4{0.f, 0.f, 0.f, 0.f};
@@ -1579,9 +1597,13 @@ __device__ __forceinline__ void reduce_row(const int64_t* __restrict__ rowptr, i
                                            float* __restrict__ x_out,
                                            const float* __restrict__ slots, unsigned& bad,
                                            SolveLds<NB>& lds, int b, int lane) {
-    const int64_t u = bounds[2 * b];
-    int b_first, b_last;
-    cut_range(rowptr, m, bounds, C, b, u, b_first, b_last);
+    const int64_t u = bounds[2 * b], nu = rowptr[u + 1] - rowptr[u];
+    // the row's last boundary: most rows have few, looked at side by side
+    const int x = b + 1 + lane;
+    const uint64_t run =
+        __ballot(x < C && bounds[2 * x] == u && bounds[2 * x + 1] > 0 && bounds[2 * x + 1] < nu);
+    int b_first = b, b_last = b + __builtin_ctzll(~run);
+    if (run == ~0ull) cut_range(rowptr, m, bounds, C, b, u, b_first, b_last);
     f4 acc[ntiles(NB)];
 #pragma unroll
     for (int t = 0; t < ntiles(NB); ++t) acc[t] = f4{0.f, 0.f, 0.f, 0.f};
@@ -1589,8 +1611,7 @@ __device__ __forceinline__ void reduce_row(const int64_t* __restrict__ rowptr, i
     // (then at entry 0), else as its last piece
     const int first_slot = (bounds[2 * (b - 1)] == u) ? 2 * (b - 1) : 2 * (b - 1) + 1;
     add_slot<NB>(acc, slots + (size_t)first_slot * slot_floats(NB), lane);
-    const int64_t nu = rowptr[u + 1] - rowptr[u];
-    if (b_last - b_first + 1 <= kPieceGroup) {
+    if (!sums_in_groups(b_last - b_first + 1, nu)) {
         add_pieces<NB>(acc, bounds, slots, b, b_last, b_last, nu, lane);
     } else {
         for (int g = b; g <= b_last; g += kPieceGroup)

@@ -39,3 +39,29 @@ def test_fixed_shares_and_claims(monkeypatch, oracle_lib, over, waves_per_cu):
     assert row_rel_err(x, xo).max() <= 1e-3
     again = gpu_half_sweep(ctx, rowptr, colidx, vals, m, n, f, 0.05, theta)
     assert np.array_equal(x, again)
+
+
+@pytest.mark.parametrize("f", [5, 40])
+@pytest.mark.parametrize("lengths", [[3000] * 5, [4096, 4097, 4353, 12_000], [200_000, 257, 90_000],
+                                     [383, 384, 385, 511, 512, 513, 640, 20, 0, 16_640]])
+def test_cut_rows_of_a_short_sweep(oracle_lib, f, lengths):
+    """Chunks smaller than the cut grid: hundreds of boundaries fall on a row's few cut points, in
+    rows just short of and past the length from which pieces are summed in two passes (4,096)."""
+    from paper_1603_03820_amd import als
+    rng = np.random.default_rng(len(lengths))
+    n = 250_000
+    rowptr = np.zeros(len(lengths) + 1, np.int64)
+    rowptr[1:] = np.cumsum(lengths)
+    colidx = np.concatenate([np.sort(rng.choice(n, size=c, replace=False))
+                             for c in lengths]).astype(np.int32)
+    vals = rng.uniform(1.0, 5.0, size=int(rowptr[-1])).astype(np.float32)
+    theta = rng.normal(0.1, 0.3, size=(n, f)).astype(np.float32)
+    m = len(lengths)
+    log(f"cut rows f={f} lengths={lengths}")
+    ctx = als.Context(0, f)
+    x = gpu_half_sweep(ctx, rowptr, colidx, vals, m, n, f, 0.05, theta)
+    xo, _ = oracle.get().half_sweep(rowptr, colidx, vals, m, n, f, 0.05, theta.astype(np.float64))
+    # fp32 sums of up to 200,000 terms, rounded once per 32: sqrt(6250) 2^-24 = 5e-6 of a Gram entry,
+    # times a condition number below 30
+    assert row_rel_err(x, xo).max() <= 1.5e-4
+    assert np.array_equal(x, gpu_half_sweep(ctx, rowptr, colidx, vals, m, n, f, 0.05, theta))
