@@ -5,10 +5,12 @@ One step = one ALS iteration on the movie-shaped workload (480,000 x 17,770, 100
 ratings, f = 100, lambda = 0.05): update-X (half-sweep on the CSR), update-Theta (half-sweep
 on the CSC) and the training RMSE, all through the C ABI of include/als.h.  Inputs are
 resident in HBM before the timed region.  `value` = half-sweeps per second over the K timed
-steps (2 per step).  Step k's RMSE (it reads X_k and Theta_k) runs on a second stream, one wave
+steps (2 per step).  A step runs its three calls one after the other on one stream.  With
+--overlap-rmse step k's RMSE (it reads X_k and Theta_k) runs on a second stream, one wave
 per SIMD, beside step k+1 (which only reads Theta_k; X and Theta are double-buffered), and
-step k+2, which overwrites X_k and Theta_k, waits for it; --serial-rmse runs it after
-update-Theta instead.
+step k+2, which overwrites X_k and Theta_k, waits for it; at f = 100 the half-sweep's waves hold
+all of a SIMD's registers, so an RMSE wave takes the place of one of them and the step is slower
+(87.4 against 99.8 half-sweeps/s).
 
 After the timed region: peak microbenchmarks (FP32 MFMA and VALU FMA rates, an HBM copy) for
 measured denominators, then the fp64 CPU oracle on a bounded row sample (all host threads, plus
@@ -71,9 +73,11 @@ def parse():
                          "alternative (gather form x last-block form), one JSON line")
     ap.add_argument("--checkpoint-every", type=int, default=5)
     ap.add_argument("--serial-rmse", action="store_true",
-                    help="run each step's RMSE after its update-Theta on the same stream (default: "
-                         "on a second stream and context, one wave per SIMD, beside the next "
-                         "step's update-X, with X double-buffered)")
+                    help="run each step's RMSE after its update-Theta on the same stream (the "
+                         "default)")
+    ap.add_argument("--overlap-rmse", action="store_true",
+                    help="run each step's RMSE on a second stream and context, one wave per SIMD, "
+                         "beside the next step's update-X, with X and Theta double-buffered")
     ap.add_argument("--other-steps", type=int, default=3,
                     help="timed steps per other workload (rank sweep, music, wiki)")
     ap.add_argument("--no-share", action="store_true",
@@ -404,8 +408,8 @@ def ablation_bench(args):
     context created under its environment setting): the gather (bounded buffer loads straight
     into MFMA operands; 64-bit global loads, the analogue of the paper's texture-cache ablation;
     theta rows staged through LDS, the analogue of its shared-memory staging), the last block
-    column (quad form vs 16x16 tiles), and where A_u accumulates (registers for the whole row vs
-    device memory every 16 ratings, the analogue of the paper's register ablation)."""
+    column (its short form vs ordinary tiles), and where A_u accumulates (registers for the whole row vs
+    device memory every 32 ratings, the analogue of the paper's register ablation)."""
     import torch
     import synth
     from paper_1603_03820_amd import als, driver
@@ -420,12 +424,12 @@ def ablation_bench(args):
     x = torch.empty((p.m, f), dtype=torch.float32, device=dev)
     th = torch.empty_like(theta0)
     variants = [
-        ("buffer", "quad", "registers", {}),
+        ("buffer", "short", "registers", {}),
         ("buffer", "tiles", "registers", {"ALS_LAST_BLOCK": "tiles"}),
-        ("global", "quad", "registers", {"ALS_GATHER": "global"}),
+        ("global", "short", "registers", {"ALS_GATHER": "global"}),
         ("global", "tiles", "registers", {"ALS_GATHER": "global", "ALS_LAST_BLOCK": "tiles"}),
         ("lds-staged", "tiles", "registers", {"ALS_GATHER": "lds"}),
-        ("buffer", "quad", "memory every 16 ratings", {"ALS_PART_ENTRIES": "16"}),
+        ("buffer", "short", "memory every 32 ratings", {"ALS_PART_ENTRIES": "32"}),
     ]
     rows = []
     for gather, last, accum, env in variants:
@@ -695,7 +699,8 @@ def main():
         print("pmc pass done", flush=True)
         return
 
-    if not args.serial_rmse:
+    overlap = args.overlap_rmse and not args.serial_rmse
+    if overlap:
         # step k: X_k <- update-X(Theta_{k-1}) into xs[k % 2]; Theta_k <- update-Theta(X_k) into
         # ths[k % 2]; then RMSE_k(X_k, Theta_k) on the side stream, where it overlaps step k+1
         # (which only reads Theta_k and writes the other buffers).  Both factors are double-
@@ -809,7 +814,7 @@ def main():
                    "m": p.m, "n": p.n, "nnz": nnz, "f": f, "lambda": p.lam,
                    "step": "update-X + update-Theta + training RMSE" + (
                        " (each RMSE on a second stream, beside the next update-X)"
-                       if not args.serial_rmse else ""),
+                       if overlap else ""),
                    "recipe": {k: v for k, v in p.recipe.items() if k not in ("m", "n", "nnz")}},
         "gflops": round(gflops, 1),
         "pct_fp32_peak": round(100.0 * gflops / 1e3 / FP32_PEAK_TFLOPS, 2),

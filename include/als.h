@@ -118,8 +118,8 @@ int als_rmse(als_ctx* ctx, const int64_t* rowptr, const int32_t* colidx, const f
    SIMD (1..8), or as many as fit (0, the default).  The entries are always cut into the same
    fixed chunks, claimed by the running waves in order, and summed per chunk in a fixed order,
    so the result does not depend on the width.  A narrow RMSE can run beside a half-sweep of
-   another context (its own workspace) on another stream: at f <= 112 the half-sweep leaves
-   room for one RMSE wave per SIMD.  ALS_ERR_INVALID_ARG outside 0..8. */
+   another context (its own workspace) on another stream; where the half-sweep's waves hold all
+   of a SIMD's registers (f from about 80 on), its waves take the place of some of them.  ALS_ERR_INVALID_ARG outside 0..8. */
 int als_rmse_waves(als_ctx* ctx, int32_t waves_per_simd);
 
 /*

@@ -32,6 +32,17 @@ def test_overlapped_step_matches_serial(config):
 
 
 @pytest.mark.gpu
+@pytest.mark.parametrize("config", ["tiny", "movie"])
+def test_overlap_option_matches_serial(config):
+    """--overlap-rmse, the step described above, against the default order of the calls."""
+    ov = _bench(config, "--overlap-rmse")
+    se = _bench(config)
+    assert "second stream" in ov["config"]["step"] and "second stream" not in se["config"]["step"]
+    assert ov["nonspd_rows"] == 0 and se["nonspd_rows"] == 0
+    assert ov["train_rmse"] == se["train_rmse"]
+
+
+@pytest.mark.gpu
 def test_bench_line_contract():
     """One JSON line with the contract's fields: the metric, whole-job value and step time,
     the roofline of the dominant kernel (frac = achieved / peak; no traffic figure for a workload
