@@ -786,7 +786,7 @@ def main():
     else:
         ach, peak, unit = ai_bytes / (herm_avg_ms * 1e-3) / 1e9, HBM_PEAK_GBS, "GB/s"
     roofline = {
-        "kernel": f"k_herm_solve<{(f + 15) // 16}> (Gram via fp32 MFMA + in-register Cholesky)",
+        "kernel": f"k_herm_solve<{(f + 15) // 16}> (Gram by bf16 part products with fp32 sums + in-register Cholesky)",
         "bound": bound, "achieved": round(ach, 3), "peak": peak,
         "unit": unit, "frac": round(ach / peak, 4),
         "traffic": traffic,
