@@ -3231,12 +3231,12 @@ int als_csr_to_csc(als_ctx* ctx, const int64_t* rowptr, const int32_t* colidx, c
     int64_t* sums = (int64_t*)base;
     int32_t* cnt = (int32_t*)(base + sums_bytes);
     // The sort runs when the entries fit beside its counters, the counting passes otherwise.  The
-    // number of entries is known on the device only: both are launched, unless no m x n matrix has
-    // too many, and the one that does not run returns at once.
+    // number of entries is known on the device only (m n does not bound it: entries with a column
+    // outside [0, n) are among them), so both are launched and the one that does not run returns at
+    // once (about 2 us a kernel).
     RxSpace rx;
-    const int64_t cap =
-        m > 0 && n > 0 ? rx_layout(base + sums_bytes, avail - sums_bytes, n, &rx) : 0;
-    const bool counting = m > 0 && n > 0 && (m > cap || n > cap || m * n > cap);
+    const bool any = m > 0 && n > 0;
+    const int64_t cap = any ? rx_layout(base + sums_bytes, avail - sums_bytes, n, &rx) : 0;
     const size_t lds_bytes = sizeof(int32_t) * (size_t)(n > 0 ? n : 1);
     const bool lds = n <= kTrLdsCols && lds_bytes <= ctx->lds_per_block;
     if (n > 0) {   // colptr: the columns' counts (of the sort), then their scan
@@ -3246,7 +3246,7 @@ int als_csr_to_csc(als_ctx* ctx, const int64_t* rowptr, const int32_t* colidx, c
     }
     if (cap > 0)
         rx_launch(rx, cap, st, rowptr, colidx, vals, m, n, colptr, (uint32_t*)rowidx, vals_t);
-    if (counting) {
+    if (any) {
         // LDS counters when one row block's fit in a workgroup's LDS
         if (lds) {
             hipError_t ea = hipFuncSetAttribute((const void*)k_tr_count_lds,
@@ -3275,7 +3275,7 @@ int als_csr_to_csc(als_ctx* ctx, const int64_t* rowptr, const int32_t* colidx, c
     hipLaunchKernelGGL(k_scan_top, dim3(1), dim3(256), 0, st, sums, (int64_t)tiles, colptr, n);
     if (n > 0)
         hipLaunchKernelGGL(k_scan_apply, dim3((unsigned)tiles), dim3(256), 0, st, colptr, n, sums);
-    if (counting) {
+    if (any) {
         if (lds)
             hipLaunchKernelGGL(k_tr_scatter_lds, dim3((unsigned)R), dim3(kWave), lds_bytes, st,
                                rowptr, colidx, vals, m, (int)n, cap, (int)R, cnt, colptr, rowidx,

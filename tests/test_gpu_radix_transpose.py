@@ -56,6 +56,18 @@ def check(ctx, m, n, rowptr, colidx, vals):
     assert np.array_equal(vt.cpu().numpy()[:k].view(np.uint32), vals[valid][order].view(np.uint32))
 
 
+def capacity(ctx, n):
+    """Entries that the sort's part of the workspace holds (n > 256): what the status block, the scan's
+    tile sums, the digit counts, the lower values' counts and starts and the arrays' alignment leave,
+    at 10 bytes an entry up to 65,536 columns and 12 beyond."""
+    def up(x):
+        return (x + 255) // 256 * 256
+    status = up(256 + 16 * 64 * 4)
+    sums = up(8 * ((n + 4095) // 4096 + 1))
+    counters = up(4 * 256 * 1536) + up(4 * 256) + up(4 << 16) + up(4 * ((1 << 16) + 1))
+    return (ctx.workspace.numel() - status - sums - counters - 4 * 256) // (10 if n <= 65_536 else 12)
+
+
 @pytest.mark.parametrize("n", [1, 255, 256, 257, 4000, 65_536, 65_537, 300_000])
 @pytest.mark.parametrize("m,nnz,shape", [(1, 1, "even"), (700, 4_095, "even"), (700, 4_096, "skewed"),
                                          (700, 4_097, "skewed"), (3, 200_000, "one_row"),
@@ -109,3 +121,20 @@ def test_both_sides_of_the_capacity(monkeypatch, n, nnz):
         log(f"radix transpose beside the counting form n={n} nnz={int(rowptr[-1])} "
             f"workspace {ctx.workspace.numel()}")
         check(ctx, 6_000, n, rowptr, colidx, vals)
+
+
+@pytest.mark.parametrize("n", [200, 2_900])
+def test_more_entries_than_the_matrix_has_places(monkeypatch, n):
+    """The first n columns of a wider CSR: the entries outside [0, n) are skipped but count towards
+    what the workspace holds, here more than it does although m n is not."""
+    from paper_1603_03820_amd import als
+    monkeypatch.setenv("ALS_WAVES_PER_CU", "1")
+    ctx = als.Context(0, 1)
+    rng = np.random.default_rng(n)
+    m, wide = 100, 4_000
+    rowptr = np.arange(m + 1, dtype=np.int64) * wide
+    colidx = np.concatenate([rng.permutation(wide) for _ in range(m)]).astype(np.int32)
+    vals = rng.standard_normal(m * wide).astype(np.float32)
+    assert n <= 256 or m * n <= capacity(ctx, n) < m * wide   # (one pass has no limit)
+    log(f"radix transpose, first {n} of {wide} columns, workspace {ctx.workspace.numel()}")
+    check(ctx, m, n, rowptr, colidx, vals)
