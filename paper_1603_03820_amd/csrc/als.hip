@@ -70,27 +70,23 @@ __device__ __forceinline__ float dpp_f(float v) {
         float, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, v), CTRL, 0xF, 0xF, false));
 }
 
-// acc + a' * b, where a' is `a` taken from lane N of the lane's 16-lane row (DPP row_newbcast:N),
-// in one v_fmac.  A DPP source needs two wait states after its last VALU write; the caller keeps
-// them (volatile, so the statements stay in source order and the caller can count).  `a` may be
-// the value of `acc` itself: as an operand of its own, a copy the register allocator makes for
-// the tied accumulator never becomes the DPP source.
-template <int N>
-__device__ __forceinline__ float fmac_bcast(float acc, float a, float b) {
-    asm volatile("v_fmac_f32_dpp %0, %1, %2 row_newbcast:%3 row_mask:0xf bank_mask:0xf"
-                 : "+v"(acc)
-                 : "v"(a), "v"(b), "n"(N));
-    return acc;
-}
-// Two wait states (for a DPP read of a register a VALU op wrote just before).
-__device__ __forceinline__ void dpp_settle() { asm volatile("s_nop 1"); }
+// No vector instruction here is inline assembly: the compiler inserts the wait states that DPP
+// reads and matrix instructions (their results, and their SrcC registers while they run) ask for, but
+// only around instructions that it knows.
 
-// -1.0 in the lanes whose bit is set in the 64-bit lane mask, else 0 (one v_cndmask; the mask
-// is a constant in scalar registers).
-__device__ __forceinline__ float lane_select_minus_one(uint64_t mask) {
-    float r;
-    asm("v_cndmask_b32_e64 %0, 0, -1.0, %1" : "=v"(r) : "s"(mask));
-    return r;
+// v taken from the lane that DPP control CTRL names (every lane of the row has one).
+template <int CTRL>
+__device__ __forceinline__ float dpp_take(float v) {
+    return __builtin_bit_cast(
+        float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), CTRL, 0xF, 0xF, true));
+}
+// v of lane N of the lane's 16-lane row (row_newbcast:N).
+template <int N>
+__device__ __forceinline__ float row_bcast(float v) { return dpp_take<0x150 + N>(v); }
+
+// Whether this lane's bit is set in a constant 64-bit lane mask.
+__device__ __forceinline__ bool in_lanes(uint64_t mask) {
+    return __builtin_amdgcn_inverse_ballot_w64(mask);
 }
 
 // Sum over the 16 lanes of a DPP row (lanes 16g..16g+15), returned to all 16 lanes with the
@@ -108,26 +104,13 @@ __device__ __forceinline__ float row_sum16(float v) {
 // halves between neighbours (xor 1), then between pairs (xor 2), so every lane keeps adding one
 // value; rotations by 4 and 8 finish the sum.  11 VALU ops against 16 for four plain row sums.
 __device__ __forceinline__ float row_sum16_t(f4 v) {
-    float v0 = v[0], v1 = v[1], v2 = v[2], v3 = v[3], t0, t1;
-    asm volatile(
-        "v_cndmask_b32_e64 %[t0], %[v1], %[v0], %[odd]\n\t"    // odd ? v0 : v1 (sent)
-        "v_cndmask_b32_e64 %[t1], %[v3], %[v2], %[odd]\n\t"    // odd ? v2 : v3 (sent)
-        "v_cndmask_b32_e64 %[v0], %[v0], %[v1], %[odd]\n\t"    // odd ? v1 : v0 (kept)
-        "v_cndmask_b32_e64 %[v2], %[v2], %[v3], %[odd]\n\t"    // odd ? v3 : v2 (kept)
-        "v_add_f32_dpp %[v0], %[t0], %[v0] quad_perm:[1,0,3,2] row_mask:0xf bank_mask:0xf\n\t"
-        "v_add_f32_dpp %[v2], %[t1], %[v2] quad_perm:[1,0,3,2] row_mask:0xf bank_mask:0xf\n\t"
-        "v_cndmask_b32_e64 %[t0], %[v2], %[v0], %[two]\n\t"    // two ? v0 : v2 (sent)
-        "v_cndmask_b32_e64 %[v0], %[v0], %[v2], %[two]\n\t"    // two ? v2 : v0 (kept)
-        "s_nop 0\n\t"
-        "v_add_f32_dpp %[v0], %[t0], %[v0] quad_perm:[2,3,0,1] row_mask:0xf bank_mask:0xf\n\t"
-        "s_nop 1\n\t"
-        "v_add_f32_dpp %[v0], %[v0], %[v0] row_ror:4 row_mask:0xf bank_mask:0xf\n\t"
-        "s_nop 1\n\t"
-        "v_add_f32_dpp %[v0], %[v0], %[v0] row_ror:8 row_mask:0xf bank_mask:0xf"
-        : [t0] "=&v"(t0), [t1] "=&v"(t1), [v0] "+v"(v0), [v1] "+v"(v1), [v2] "+v"(v2),
-          [v3] "+v"(v3)
-        : [odd] "s"(0xAAAAAAAAAAAAAAAAull), [two] "s"(0xCCCCCCCCCCCCCCCCull));
-    return v0;
+    const bool odd = in_lanes(0xAAAAAAAAAAAAAAAAull), two = in_lanes(0xCCCCCCCCCCCCCCCCull);
+    const float a0 = (odd ? v[1] : v[0]) + dpp_take<0xB1>(odd ? v[0] : v[1]);   // quad_perm [1,0,3,2]
+    const float a2 = (odd ? v[3] : v[2]) + dpp_take<0xB1>(odd ? v[2] : v[3]);
+    float s = (two ? a2 : a0) + dpp_take<0x4E>(two ? a0 : a2);                  // quad_perm [2,3,0,1]
+    s += dpp_take<0x124>(s);                                                    // row_ror:4
+    s += dpp_take<0x128>(s);                                                    // row_ror:8
+    return s;
 }
 
 // ------------------------------------------------------------------------------- plan ----
@@ -999,7 +982,11 @@ struct FactorRegs {
 
 // Pivot kk = 4 B + P of factor_tile.  The next pivot waits on this one's readlane, s, s^2, the
 // product for the next row and that row's update, so the next row (P + 1) is updated first.
-// One transcendental per pivot (s = piv^{-1/2}; 1/piv = s^2).
+// One transcendental per pivot (s = piv^{-1/2}; 1/piv = s^2).  A row's multiplier is one v_mov_b32_dpp
+// for its two FMAs; the FMA that reads it by DPP itself exists only as inline assembly here, with
+// wait states kept by hand, and was no faster with the waits that the matrix instructions before it
+// ask for (movie user side f = 100 10.02 ms both ways, f = 32 1.83 against 1.86 here, f = 128 22.8
+// against 22.5; 1/32 of the wiki user side 21.3 against 21.0).
 template <int B, int P, bool kFull>
 __device__ __forceinline__ void factor_pivot(FactorRegs& R, bool live, int& pmin, int& pmax,
                                              float* ystore) {
@@ -1016,29 +1003,17 @@ __device__ __forceinline__ void factor_pivot(FactorRegs& R, bool live, int& pmin
     const float aw = s2 * R.wr[P];          // (-W)[kk][c] / piv
     if (ystore) ystore[kk] = -s * R.tr[P];  // L[nlast][kk] = s T[kk][nlast]
     R.wr[P] *= s;                           // row kk of -W is final
-    // Order: row P + 1 (W, then T: the W update reads T's column kk before the T update changes
-    // it), then the other rows' W updates, then their T updates.  A DPP read of a T register then
-    // sits at least n - 1 instructions after the previous pivot's write of it (n row updates
-    // here); a block's first pivot always waits (its sources were loaded or carried over the
-    // block's branch).
-    // (without the later rows, kFull = false, every pivot waits)
-    constexpr int n = (3 - P) + (3 - B);
-    if constexpr (P == 0 || n < 3 || !kFull) dpp_settle();
-    if constexpr (P < 3) {
-        R.wr[P + 1] = fmac_bcast<kk>(R.wr[P + 1], R.tr[P + 1], aw);
-        R.tr[P + 1] = fmac_bcast<kk>(R.tr[P + 1], R.tr[P + 1], at);
-    }
+    // a later row's N[i][kk], in its lane kk, serves both of the row's updates
+    const auto update = [&](float& t, float& w) {
+        const float a = row_bcast<kk>(t);
+        w = __builtin_fmaf(a, aw, w);
+        t = __builtin_fmaf(a, at, t);
+    };
 #pragma unroll
-    for (int j = P + 2; j < 4; ++j) R.wr[j] = fmac_bcast<kk>(R.wr[j], R.tr[j], aw);
+    for (int j = P + 1; j < 4; ++j) update(R.tr[j], R.wr[j]);
     if constexpr (kFull) {
 #pragma unroll
-        for (int bb = B + 1; bb < 4; ++bb) R.wo[bb] = fmac_bcast<kk>(R.wo[bb], R.to[bb], aw);
-    }
-#pragma unroll
-    for (int j = P + 2; j < 4; ++j) R.tr[j] = fmac_bcast<kk>(R.tr[j], R.tr[j], at);
-    if constexpr (kFull) {
-#pragma unroll
-        for (int bb = B + 1; bb < 4; ++bb) R.to[bb] = fmac_bcast<kk>(R.to[bb], R.to[bb], at);
+        for (int bb = B + 1; bb < 4; ++bb) update(R.to[bb], R.wo[bb]);
     }
 }
 
@@ -1055,9 +1030,8 @@ __device__ __forceinline__ void factor_pivot(FactorRegs& R, bool live, int& pmin
 // current block is replicated).  Between blocks the groups trade the next block's rows through
 // LDS.  Columns left of the pivot are not needed again; they go to zero as the elimination
 // proceeds instead of being masked.  npiv real pivots: a block with none is skipped (last block
-// only) and a pivot past npiv inside a block runs with s = 0, so it adds nothing (a branch per
-// pivot would make the register allocator copy DPP sources right before their reads); rows of W
-// past npiv stay as the updates left them (the identity in the padding, zero for a pivot skipped
+// only) and a pivot past npiv inside a block runs with s = 0, so it adds nothing (no branch per
+// pivot); rows of W past npiv stay as the updates left them (the identity in the padding, zero for a pivot skipped
 // inside a block).  In the last block the row nlast is the augmented b row, whose L entries are y
 // (written to S.y).  pmin/pmax track the pivots' bit patterns: every pivot was positive and
 // finite (not NaN, not +inf) iff pmin > 0 and pmax < the bits of +inf.
@@ -1107,14 +1081,14 @@ __device__ __forceinline__ void factor_tile(SolveLds<NB>& S, int K, int npiv, in
     for (int j = 0; j < 4; ++j) R.tr[j] = S.T[c * 16 + j];
     // -identity: row j in lanes c == j; row 4b' + g in lanes 16 g + 4 b' + g
 #pragma unroll
-    for (int j = 0; j < 4; ++j) R.wr[j] = lane_select_minus_one(0x0001000100010001ull << j);
+    for (int j = 0; j < 4; ++j) R.wr[j] = in_lanes(0x0001000100010001ull << j) ? -1.f : 0.f;
     R.to[0] = R.wo[0] = 0.f;
     if constexpr (kFull) {
 #pragma unroll
         for (int bb = 1; bb < 4; ++bb) R.to[bb] = S.T[c * 16 + 4 * bb + g];
 #pragma unroll
         for (int bb = 1; bb < 4; ++bb)
-            R.wo[bb] = lane_select_minus_one(0x0008000400020001ull << (4 * bb));
+            R.wo[bb] = in_lanes(0x0008000400020001ull << (4 * bb)) ? -1.f : 0.f;
     } else {
 #pragma unroll
         for (int bb = 1; bb < 4; ++bb) R.to[bb] = R.wo[bb] = 0.f;

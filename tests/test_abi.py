@@ -153,6 +153,70 @@ def test_dpp_sources_settled():
     assert len(dpp_violations(planted)) == 1
 
 
+# Wait states after a matrix instruction before a VALU instruction may read or write its result
+# (passes of 4 cycles plus 2 for the fp32 products, plus 3 for the bf16 ones).
+MFMA_WAITS = {"v_mfma_f32_16x16x4_f32": 10, "v_mfma_f32_16x16x32_bf16": 7}
+
+
+def _registers(tok):
+    """The vector registers (v or a) that an operand names."""
+    tok = tok.split()[0].strip("-|") if tok else ""
+    return {(tok[0], r) for r in _vgprs("v" + tok[1:])} if tok[:1] in ("v", "a") else set()
+
+
+def mfma_violations(text):
+    """VALU instructions that read or write a register of a matrix instruction's result before it is
+    there: fewer wait states after it than MFMA_WAITS (s_nop N counts N + 1, any other instruction 1).
+    The compiler keeps them around instructions it knows, but not around inline assembly."""
+    bad, hist = [], []
+    for line in text.splitlines():
+        t = line.split("//")[0].strip()
+        if t.endswith(">:"):
+            hist = []
+            continue
+        if not t or t.endswith(":"):
+            continue
+        op = t.split()[0]
+        if op in ("s_branch", "s_endpgm"):   # control does not reach what follows
+            hist = []
+            continue
+        if op == "s_nop":
+            hist = (hist + [(set(), 0, int(t.split()[1], 0) + 1)])[-16:]
+            continue
+        args = [a.strip() for a in t[len(op):].split(",")]
+        if op.startswith("v_mfma"):
+            assert op in MFMA_WAITS, op
+            hist = (hist + [(_registers(args[0]), MFMA_WAITS[op], 1)])[-16:]
+            continue
+        if op.startswith("v_"):
+            used = set().union(*(_registers(a) for a in args))
+            ws = 0
+            for result, need, n in reversed(hist):
+                if ws < need and result & used:
+                    bad.append(t)
+                    break
+                ws += n
+        hist = (hist + [(set(), 0, 1)])[-16:]
+    return bad
+
+
+def test_mfma_results_settled():
+    """No VALU instruction touches a matrix instruction's result too early, none is inline assembly
+    (whose wait states nobody inserts), and the check catches a planted violation."""
+    source = open(os.path.join(ROOT, "paper_1603_03820_amd", "csrc", "als.hip")).read()
+    for statement in re.findall(r"\basm\b[^;]*;", source):
+        assert not re.search(r'"[^"]*\bv_', statement), statement
+    if not os.path.exists("/opt/rocm/llvm/bin/clang-offload-bundler"):
+        pytest.skip("ROCm LLVM tools not installed")
+    planted = ("<k>:\n\tv_mfma_f32_16x16x4_f32 v[10:13], v4, v4, v[18:21]\n\ts_nop 8\n"
+               "\tv_cndmask_b32_e64 v13, 0, -1.0, s[0:1]\n")
+    assert len(mfma_violations(planted)) == 1
+    assert mfma_violations(planted.replace("s_nop 8", "s_nop 9")) == []
+    text = _device_disassembly()
+    assert text.count("v_mfma") > 1000
+    assert mfma_violations(text) == []
+
+
 def test_bench_refuses_more_than_one_gpu():
     """bench.py --gpus N > 1 exits with a message before touching a GPU."""
     import json
