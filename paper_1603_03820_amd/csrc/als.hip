@@ -70,9 +70,24 @@ __device__ __forceinline__ float dpp_f(float v) {
         float, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, v), CTRL, 0xF, 0xF, false));
 }
 
-// No vector instruction here is inline assembly: the compiler inserts the wait states that DPP
-// reads and matrix instructions (their results, and their SrcC registers while they run) ask for, but
-// only around instructions that it knows.
+// acc + a' * b, where a' is `a` taken from lane N of the lane's 16-lane row (DPP row_newbcast:N),
+// in one v_fmac.  The only vector instruction here that is inline assembly, around which the compiler
+// inserts no wait states.  A DPP source needs two of them after its last VALU write; the caller keeps
+// them (volatile, so the statements stay in source order and the caller can count).  A matrix
+// instruction's result needs ten; factor_tile keeps those.  (As update_dpp and an FMA it becomes a DPP
+// move for two FMAs and up to 20 registers more: ranks up to 16 lose a resident wave or two, f = 16
+// 326 -> 365 us on 20M ratings of 200,000 users, f = 32 on the movie user side 1.79 -> 1.86 ms; f = 128
+// and short rows gain 1%.)  `a` may be the value of `acc` itself: as an operand of its own, a copy
+// the register allocator makes for the tied accumulator never becomes the DPP source.
+template <int N>
+__device__ __forceinline__ float fmac_bcast(float acc, float a, float b) {
+    asm volatile("v_fmac_f32_dpp %0, %1, %2 row_newbcast:%3 row_mask:0xf bank_mask:0xf"
+                 : "+v"(acc)
+                 : "v"(a), "v"(b), "n"(N));
+    return acc;
+}
+// Two wait states (for a DPP read of a register a VALU op wrote just before).
+__device__ __forceinline__ void dpp_settle() { asm volatile("s_nop 1"); }
 
 // v taken from the lane that DPP control CTRL names (every lane of the row has one).
 template <int CTRL>
@@ -80,10 +95,6 @@ __device__ __forceinline__ float dpp_take(float v) {
     return __builtin_bit_cast(
         float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), CTRL, 0xF, 0xF, true));
 }
-// v of lane N of the lane's 16-lane row (row_newbcast:N).
-template <int N>
-__device__ __forceinline__ float row_bcast(float v) { return dpp_take<0x150 + N>(v); }
-
 // Whether this lane's bit is set in a constant 64-bit lane mask.
 __device__ __forceinline__ bool in_lanes(uint64_t mask) {
     return __builtin_amdgcn_inverse_ballot_w64(mask);
@@ -982,11 +993,7 @@ struct FactorRegs {
 
 // Pivot kk = 4 B + P of factor_tile.  The next pivot waits on this one's readlane, s, s^2, the
 // product for the next row and that row's update, so the next row (P + 1) is updated first.
-// One transcendental per pivot (s = piv^{-1/2}; 1/piv = s^2).  A row's multiplier is one v_mov_b32_dpp
-// for its two FMAs; the FMA that reads it by DPP itself exists only as inline assembly here, with
-// wait states kept by hand, and was no faster with the waits that the matrix instructions before it
-// ask for (movie user side f = 100 10.02 ms both ways, f = 32 1.83 against 1.86 here, f = 128 22.8
-// against 22.5; 1/32 of the wiki user side 21.3 against 21.0).
+// One transcendental per pivot (s = piv^{-1/2}; 1/piv = s^2).
 template <int B, int P, bool kFull>
 __device__ __forceinline__ void factor_pivot(FactorRegs& R, bool live, int& pmin, int& pmax,
                                              float* ystore) {
@@ -1003,17 +1010,29 @@ __device__ __forceinline__ void factor_pivot(FactorRegs& R, bool live, int& pmin
     const float aw = s2 * R.wr[P];          // (-W)[kk][c] / piv
     if (ystore) ystore[kk] = -s * R.tr[P];  // L[nlast][kk] = s T[kk][nlast]
     R.wr[P] *= s;                           // row kk of -W is final
-    // a later row's N[i][kk], in its lane kk, serves both of the row's updates
-    const auto update = [&](float& t, float& w) {
-        const float a = row_bcast<kk>(t);
-        w = __builtin_fmaf(a, aw, w);
-        t = __builtin_fmaf(a, at, t);
-    };
+    // Order: row P + 1 (W, then T: the W update reads T's column kk before the T update changes
+    // it), then the other rows' W updates, then their T updates.  A DPP read of a T register then
+    // sits at least n - 1 instructions after the previous pivot's write of it (n row updates
+    // here); a block's first pivot always waits (its sources were loaded or carried over the
+    // block's branch).
+    // (without the later rows, kFull = false, every pivot waits)
+    constexpr int n = (3 - P) + (3 - B);
+    if constexpr (P == 0 || n < 3 || !kFull) dpp_settle();
+    if constexpr (P < 3) {
+        R.wr[P + 1] = fmac_bcast<kk>(R.wr[P + 1], R.tr[P + 1], aw);
+        R.tr[P + 1] = fmac_bcast<kk>(R.tr[P + 1], R.tr[P + 1], at);
+    }
 #pragma unroll
-    for (int j = P + 1; j < 4; ++j) update(R.tr[j], R.wr[j]);
+    for (int j = P + 2; j < 4; ++j) R.wr[j] = fmac_bcast<kk>(R.wr[j], R.tr[j], aw);
     if constexpr (kFull) {
 #pragma unroll
-        for (int bb = B + 1; bb < 4; ++bb) update(R.to[bb], R.wo[bb]);
+        for (int bb = B + 1; bb < 4; ++bb) R.wo[bb] = fmac_bcast<kk>(R.wo[bb], R.to[bb], aw);
+    }
+#pragma unroll
+    for (int j = P + 2; j < 4; ++j) R.tr[j] = fmac_bcast<kk>(R.tr[j], R.tr[j], at);
+    if constexpr (kFull) {
+#pragma unroll
+        for (int bb = B + 1; bb < 4; ++bb) R.to[bb] = fmac_bcast<kk>(R.to[bb], R.to[bb], at);
     }
 }
 
@@ -1030,8 +1049,9 @@ __device__ __forceinline__ void factor_pivot(FactorRegs& R, bool live, int& pmin
 // current block is replicated).  Between blocks the groups trade the next block's rows through
 // LDS.  Columns left of the pivot are not needed again; they go to zero as the elimination
 // proceeds instead of being masked.  npiv real pivots: a block with none is skipped (last block
-// only) and a pivot past npiv inside a block runs with s = 0, so it adds nothing (no branch per
-// pivot); rows of W past npiv stay as the updates left them (the identity in the padding, zero for a pivot skipped
+// only) and a pivot past npiv inside a block runs with s = 0, so it adds nothing (a branch per
+// pivot would make the register allocator copy DPP sources right before their reads); rows of W
+// past npiv stay as the updates left them (the identity in the padding, zero for a pivot skipped
 // inside a block).  In the last block the row nlast is the augmented b row, whose L entries are y
 // (written to S.y).  pmin/pmax track the pivots' bit patterns: every pivot was positive and
 // finite (not NaN, not +inf) iff pmin > 0 and pmax < the bits of +inf.
@@ -1077,15 +1097,23 @@ __device__ __forceinline__ void factor_tile(SolveLds<NB>& S, int K, int npiv, in
                                             int& pmin, int& pmax, int lane) {
     const int g = lane >> 4, c = lane & 15;
     FactorRegs R;
+    // No matrix instruction moves past this point, and the first inline FMA comes ten wait states after
+    // it, while the tile loads from LDS (the panel's and trailing products may have results still
+    // under way, or be reading SrcC registers that are given out again here).
+    __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
     for (int j = 0; j < 4; ++j) R.tr[j] = S.T[c * 16 + j];
-    // -identity: row j in lanes c == j; row 4b' + g in lanes 16 g + 4 b' + g
-#pragma unroll
-    for (int j = 0; j < 4; ++j) R.wr[j] = in_lanes(0x0001000100010001ull << j) ? -1.f : 0.f;
     R.to[0] = R.wo[0] = 0.f;
     if constexpr (kFull) {
 #pragma unroll
         for (int bb = 1; bb < 4; ++bb) R.to[bb] = S.T[c * 16 + 4 * bb + g];
+    }
+    __builtin_amdgcn_sched_barrier(0);
+    asm volatile("s_nop 9");
+    // -identity: row j in lanes c == j; row 4b' + g in lanes 16 g + 4 b' + g
+#pragma unroll
+    for (int j = 0; j < 4; ++j) R.wr[j] = in_lanes(0x0001000100010001ull << j) ? -1.f : 0.f;
+    if constexpr (kFull) {
 #pragma unroll
         for (int bb = 1; bb < 4; ++bb)
             R.wo[bb] = in_lanes(0x0008000400020001ull << (4 * bb)) ? -1.f : 0.f;
