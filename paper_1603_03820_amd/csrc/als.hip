@@ -583,8 +583,15 @@ constexpr int gram_registers(int nb, int last) {
     return 4 * gram_tiles(nb, last) + 12 * (last == kLastTiles ? nb : nb - 1) +
            (last == kLastPacked ? 4 : 0) + (last == kLastRating ? nb - 1 : 0);
 }
-// Two waves per SIMD where accumulators and parts leave 50 registers of 256 for the rest.
-constexpr int gram_waves(int nb, int last) { return gram_registers(nb, last) <= 206 ? 2 : 1; }
+// The least waves per SIMD that the compiler is held to: two where accumulators and parts leave 50
+// registers of 256 for the rest, and what f = 16, 32 and 48 take without spilling (the 64-bit parts
+// form, whose waves bound the others', would take 102 and 130 registers at f = 16 and 32 and lose one
+// of five and of four waves: 361 against 327 us on 20M ratings of 200,000 users at f = 16, 659 against
+// 573 at f = 32).
+constexpr int gram_waves(int nb, int last) {
+    if (nb <= 4 && last == kLastRating) return 7 - nb;
+    return gram_registers(nb, last) <= 206 ? 2 : 1;
+}
 
 // The gathered values of a group, step by step.
 template <class G>
@@ -895,7 +902,10 @@ __device__ __forceinline__ void group_loop(const G& gat, const int32_t* __restri
         const typename G::Entry* next = odd ? cur : cur + kGroupEntries;
         if (last) next = cur;
         if (last ? more : odd) {
-            ring[other * kGramBatch + lane] = last ? next_first : nq;
+            // (by members: a choice between the objects is one between addresses, and keeps both in
+            // private memory)
+            ring[other * kGramBatch + lane] =
+                typename G::Entry{last ? next_first.e : nq.e, last ? next_first.r : nq.r};
             __syncthreads();
             next = ring + other * kGramBatch;
         }

@@ -37,7 +37,7 @@ def test_strerror_without_device():
     assert als._lib.als_strerror(12345) == b"unknown status"
 
 
-def _device_disassembly(lib=None):
+def _device_disassembly(lib=None, tool=("llvm-objdump", "-d")):
     import subprocess
     import tempfile
     from paper_1603_03820_amd import build
@@ -50,8 +50,34 @@ def _device_disassembly(lib=None):
         subprocess.run([f"{llvm}/clang-offload-bundler", "--unbundle", "--type=o",
                         f"--input={fat}", "--targets=hipv4-amdgcn-amd-amdhsa--gfx950",
                         f"--output={co}"], check=True)
-        return subprocess.run([f"{llvm}/llvm-objdump", "-d", co], capture_output=True,
+        return subprocess.run([f"{llvm}/{tool[0]}", *tool[1:], co], capture_output=True,
                               text=True, check=True).stdout
+
+
+def _kernel_facts():
+    """The library's kernels: name -> the numbers of its metadata."""
+    kernels, facts = {}, {}
+    for line in _device_disassembly(tool=("llvm-readelf", "--notes")).splitlines():
+        if re.match(r"\s+- \.(agpr_count|args):", line):
+            facts = {}
+        m = re.match(r"[\s-]*\.(\w+):\s+(\S+)", line)
+        if m and m.group(1) == "name" and m.group(2).startswith("_Z"):
+            kernels[m.group(2)] = facts
+        elif m and m.group(2).isdigit():
+            facts[m.group(1)] = int(m.group(2))
+    return kernels
+
+
+def test_private_memory_is_spills_only():
+    """No kernel keeps an object in private memory: scratch is what spilled registers need, 4 bytes
+    each (and at most 16 of alignment)."""
+    if not os.path.exists("/opt/rocm/llvm/bin/clang-offload-bundler"):
+        pytest.skip("ROCm LLVM tools not installed")
+    kernels = _kernel_facts()
+    assert sum("k_herm_solve" in k for k in kernels) > 100
+    over = {k: v for k, v in kernels.items()
+            if v["private_segment_fixed_size"] > 4 * v["vgpr_spill_count"] + 16}
+    assert not over, over
 
 
 def test_device_code_shape():
