@@ -180,8 +180,9 @@ def test_dpp_sources_settled():
 
 
 # Wait states after a matrix instruction before a VALU instruction may read or write its result
-# (passes of 4 cycles plus 2 for the fp32 products, plus 3 for the bf16 ones).
+# (passes of 4 cycles plus 2 for the fp32 products, plus 3 for the bf16 ones), kept for its SrcC too.
 MFMA_WAITS = {"v_mfma_f32_16x16x4_f32": 10, "v_mfma_f32_16x16x32_bf16": 7}
+INLINE = "v_fmac_f32_dpp"   # the only vector instruction that is inline assembly
 
 
 def _registers(tok):
@@ -191,9 +192,9 @@ def _registers(tok):
 
 
 def mfma_violations(text):
-    """VALU instructions that read or write a register of a matrix instruction's result before it is
-    there: fewer wait states after it than MFMA_WAITS (s_nop N counts N + 1, any other instruction 1).
-    The compiler keeps them around instructions it knows, but not around inline assembly."""
+    """Inline instructions that touch a register of a matrix instruction's result, or write one of its
+    SrcC, with fewer wait states after it than MFMA_WAITS (s_nop N counts N + 1, any other
+    instruction 1).  The compiler keeps them around the instructions it knows."""
     bad, hist = [], []
     for line in text.splitlines():
         t = line.split("//")[0].strip()
@@ -206,40 +207,39 @@ def mfma_violations(text):
         if op in ("s_branch", "s_endpgm"):   # control does not reach what follows
             hist = []
             continue
+        args = [_registers(a.strip()) for a in t[len(op):].split(",")]
+        result, addend, need, states = set(), set(), 0, 1
         if op == "s_nop":
-            hist = (hist + [(set(), 0, int(t.split()[1], 0) + 1)])[-16:]
-            continue
-        args = [a.strip() for a in t[len(op):].split(",")]
-        if op.startswith("v_mfma"):
-            assert op in MFMA_WAITS, op
-            hist = (hist + [(_registers(args[0]), MFMA_WAITS[op], 1)])[-16:]
-            continue
-        if op.startswith("v_"):
-            used = set().union(*(_registers(a) for a in args))
+            states = int(t.split()[1], 0) + 1
+        elif op.startswith("v_mfma"):
+            result, addend, need = args[0], args[3], MFMA_WAITS[op]
+        elif op == INLINE:
             ws = 0
-            for result, need, n in reversed(hist):
-                if ws < need and result & used:
+            for r, c, wait, n in reversed(hist):
+                if ws < wait and (r & set().union(*args) or c & args[0]):
                     bad.append(t)
                     break
                 ws += n
-        hist = (hist + [(set(), 0, 1)])[-16:]
+        hist = (hist + [(result, addend, need, states)])[-16:]
     return bad
 
 
 def test_mfma_results_settled():
-    """No VALU instruction touches a matrix instruction's result too early, the factor's DPP FMA is the
-    only one that is inline assembly (whose wait states the compiler does not insert), and the check
-    catches a planted violation."""
+    """The factor's DPP FMA is the only vector instruction that is inline assembly (the compiler inserts
+    no wait states around it), it comes late enough after every matrix instruction, and the check
+    catches planted violations."""
     source = open(os.path.join(ROOT, "paper_1603_03820_amd", "csrc", "als.hip")).read()
-    assert set(re.findall(r'\basm\b[^"]*"(v_\w+)', source)) == {"v_fmac_f32_dpp"}
+    assert set(re.findall(r'\basm\b[^"]*"(v_\w+)', source)) == {INLINE}
     if not os.path.exists("/opt/rocm/llvm/bin/clang-offload-bundler"):
         pytest.skip("ROCm LLVM tools not installed")
     planted = ("<k>:\n\tv_mfma_f32_16x16x4_f32 v[10:13], v4, v4, v[18:21]\n\ts_nop 8\n"
-               "\tv_cndmask_b32_e64 v13, 0, -1.0, s[0:1]\n")
-    assert len(mfma_violations(planted)) == 1
-    assert mfma_violations(planted.replace("s_nop 8", "s_nop 9")) == []
+               "\tv_fmac_f32_dpp v{}, v30, v31 row_newbcast:1 row_mask:0xf bank_mask:0xf\n")
+    assert len(mfma_violations(planted.format(13))) == 1
+    assert len(mfma_violations(planted.format(18))) == 1
+    assert mfma_violations(planted.format(4)) == []
+    assert mfma_violations(planted.format(13).replace("s_nop 8", "s_nop 9")) == []
     text = _device_disassembly()
-    assert text.count("v_mfma") > 1000
+    assert text.count("v_mfma") > 1000 and text.count(INLINE) > 1000
     assert mfma_violations(text) == []
 
 
