@@ -513,12 +513,19 @@ __device__ __forceinline__ void pipe_loop(const G& gat, const int32_t* __restric
 // The Gram's products run on the bf16 matrix units with every fp32 value split exactly into three
 // bf16 parts, x = h + m + l (h: the upper 16 bits of x; m, l: the rest rounded to nearest, twice; 8
 // significant bits each), and six of the nine part products kept: hh, hm, mh, mm, hl, lh.  The
-// dropped ml, lm, ll are below 2^-23 of hh, 2^-26 on average and of random sign, under the
-// rounding of an fp32 product sum.  Part products are exact in fp32.  A group of 32 entries is one K = 32
-// step: its products start from zero, smallest parts first, and their sum is added to the fp32
-// accumulator once, so that an accumulator is rounded once per 32 entries (the fp32
-// v_mfma_f32_16x16x4_f32 rounds it for every entry): against fp64 the Gram errs less than the
-// fp32 form at every length.
+// dropped ml and lm reach 2^-23 of hh each, 2^-22 together (2.4e-8 as a root mean square over
+// random values), and have one sign for equal values.  Part products are exact in fp32.  A group of 32
+// entries is one K = 32 step: its products start from zero, smallest parts first, and their sum is
+// added to the fp32 accumulator once, so that an accumulator is rounded once per 32 entries (the fp32
+// v_mfma_f32_16x16x4_f32 rounds it for every entry).  The sums' error against fp64, relative, as a root
+// mean square, beside one FMA per entry: 3.0e-8 (4.5e-8) for 8 random entries, 2.6e-8 (8.4e-8) for 32,
+// 4.0e-8 (1.7e-7) for 128; for as many equal entries 3.9e-8 (5.3e-8), 3.7e-8 (2.3e-7), 3.9e-8 (9.5e-7).  Only the shortest sums
+// lose: 4.3e-8 (2.5e-8) for one entry.  So a piece of at most kPlainEntries = 16 entries, up to which
+// the dropped products may also exceed the FMAs' largest error, takes fp32 products instead: before
+// its group runs, from the same gathered values, and the group then runs with parts of zero (a
+// group of its own would cost registers that f = 80 to 112 do not have: spills, movie user side
+// 9.9 -> 10.7 ms, 1/32 of the wiki one 21.1 -> 23.5).  Rows of 5 ratings on average pay 2-6% for it, the
+// wiki part (62) 0.9%, the movie sides nothing.
 //
 // Why: v_mfma_f32_16x16x4_f32 takes 32 cycles for 4 entries of a tile, 256 cycles for 32, and
 // nothing else runs on the SIMD meanwhile (fp32 MFMA and VALU work exclude each other).  Six
@@ -542,6 +549,7 @@ __device__ __forceinline__ void pipe_loop(const G& gat, const int32_t* __restric
 // are added when the Gram is complete (fold_packed).
 constexpr int kGroupSteps = 8;
 constexpr int kGroupEntries = 4 * kGroupSteps;
+constexpr int kPlainEntries = 16;              // pieces up to this long take fp32 products
 constexpr int kGramBatch = kWave;              // index batch: one entry per lane, two groups
 constexpr int kGramRing = 2 * kGramBatch;
 
@@ -550,14 +558,21 @@ typedef float f2 __attribute__((ext_vector_type(2)));
 typedef __bf16 bf2 __attribute__((ext_vector_type(2)));
 typedef __bf16 bf8 __attribute__((ext_vector_type(8)));
 
+// How split_pair takes h: the kept bits of a value, and the v_perm selector of two values' upper halves.
+// With kNothing all three parts are zero (for finite values).
+struct Cut {
+    unsigned bits, pick;
+};
+constexpr Cut kUpperHalf{0xFFFF0000u, 0x07060302u}, kNothing{0xFFFFFFFFu, 0x0C0C0C0Cu};
+
 // The three parts of x and y, packed (x in the low half).  h is cut, not rounded, so that no
 // finite value's parts overflow.
-__device__ __forceinline__ void split_pair(float x, float y, unsigned& h, unsigned& m,
+__device__ __forceinline__ void split_pair(float x, float y, const Cut& cut, unsigned& h, unsigned& m,
                                            unsigned& l) {
     const unsigned xb = __builtin_bit_cast(unsigned, x), yb = __builtin_bit_cast(unsigned, y);
-    h = __builtin_amdgcn_perm(yb, xb, 0x07060302u);
-    const float rx = x - __builtin_bit_cast(float, xb & 0xFFFF0000u);
-    const float ry = y - __builtin_bit_cast(float, yb & 0xFFFF0000u);
+    h = __builtin_amdgcn_perm(yb, xb, cut.pick);
+    const float rx = x - __builtin_bit_cast(float, xb & cut.bits);
+    const float ry = y - __builtin_bit_cast(float, yb & cut.bits);
     m = __builtin_bit_cast(unsigned, __builtin_convertvector(f2{rx, ry}, bf2));
     const float sx = rx - __builtin_bit_cast(float, m << 16);
     const float sy = ry - __builtin_bit_cast(float, m & 0xFFFF0000u);
@@ -793,7 +808,7 @@ __device__ __forceinline__ void fold_rating(f4 (&acc)[ntiles(NB)], const float (
 
 template <int NB, int LAST, class G, bool PARTS>
 struct GramBody {
-    static constexpr bool kParts = PARTS;
+    static constexpr bool kParts = PARTS, kPlain = true;
     static constexpr int kTop = LAST == kLastRating ? NB - 2 : NB - 1;   // last column of products
     int part_mask;        // groups per part - 1 (a power of two - 1)
     const G& gat;
@@ -803,6 +818,7 @@ struct GramBody {
     void* scratch;        // LDS for fold_packed and fold_rating
     float* wslot;         // the wave's slot
     int lane;
+    Cut cut = kUpperHalf; // kNothing: the piece's products are in acc already (plain)
     float b[NB > 1 ? NB - 1 : 1];   // kLastRating: the rating column's sums
     Parts<NB, LAST> a;
     // the accumulators from zero (those of the last block column are set by finish where no
@@ -817,6 +833,29 @@ struct GramBody {
             for (int I = 0; I < NB - 1; ++I) b[I] = 0.f;
         }
     }
+    // the products of a piece of at most 4 kSteps entries in fp32, four entries a step, into the
+    // accumulators (the rating column of kLastRating is take's)
+    template <int kSteps>
+    __device__ __forceinline__ void plain(const Raw<G>& raw, const typename G::Entry* ring, int g) {
+        float x[kSteps][G::kBlocks];
+#pragma unroll
+        for (int j = 0; j < kSteps; ++j) {
+            const float r = ring[4 * j + g].r;
+            gat.operands(raw.b[j], r, x[j]);
+            // a packed last block's copies of its columns add nothing
+            if constexpr (LAST == kLastPacked) x[j][NB - 1] = third == 0 ? x[j][NB - 1] : 0.f;
+        }
+#pragma unroll
+        for (int I = 0; I <= kTop; ++I)
+#pragma unroll
+            for (int J = I; J <= kTop; ++J) {
+                f4 t = f4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+                for (int j = 0; j < kSteps; ++j)
+                    t = __builtin_amdgcn_mfma_f32_16x16x4f32(x[j][I], x[j][J], t, 0, 0, 0);
+                acc[tu(NB, I, J)] = t;
+            }
+    }
     // the group's operands from its gathered values and its ratings (in the ring)
     __device__ __forceinline__ void take(const Raw<G>& raw, const typename G::Entry* ring) {
         const int g = lane >> 4;
@@ -829,7 +868,7 @@ struct GramBody {
 #pragma unroll
             for (int I = 0; I < G::kBlocks; ++I) {
                 unsigned h, m, l;
-                split_pair(x[I], y[I], h, m, l);
+                split_pair(x[I], y[I], cut, h, m, l);
                 if constexpr (LAST == kLastRating)
                     b[I] = __builtin_fmaf(y[I], ry, __builtin_fmaf(x[I], rx, b[I]));
                 if (LAST == kLastPacked && I == NB - 1) {
@@ -886,6 +925,16 @@ __device__ __forceinline__ void group_loop(const G& gat, const int32_t* __restri
     // a row has fewer than 2^31 entries (its columns are distinct int32 indices)
     const int total = (int)(kend - kbeg);
     const int ngroups = (total + kGroupEntries - 1) / kGroupEntries;
+    if constexpr (Body::kPlain) {
+        if (total <= kPlainEntries) {
+            int l = lane;   // (opaque: addresses from it are not kept in registers across rows)
+            asm volatile("" : "+v"(l));
+            const typename G::Entry* cur = ring + slot * kGramBatch;
+            if (total <= kPlainEntries / 2) body.template plain<kPlainEntries / 8>(raw, cur, l >> 4);
+            else body.template plain<kPlainEntries / 4>(raw, cur, l >> 4);
+            body.cut = kNothing;
+        }
+    }
     typename G::Entry nq{};
     for (int q = 0; q < ngroups; ++q) {
         if constexpr (Body::kParts) {
@@ -926,7 +975,7 @@ constexpr int dump_floats() { return 16 * (NB + 3); }
 
 template <int NB, int LAST, class G>
 struct DumpBody {
-    static constexpr bool kParts = false;
+    static constexpr bool kParts = false, kPlain = false;
     const G& gat;
     float* __restrict__ out;
     int64_t limit;   // entries that fit in out

@@ -1,12 +1,12 @@
 """The Gram by bf16 part products: row lengths around the 32-entry group and the 64-entry index
 batch, every form of the last block column (rating alone, packed, ordinary tiles) and both gather
-forms, against the fp64 oracle; values near the top of the fp32 range; and the accuracy of long
-and of cancelling sums against fp64.
+forms, against the fp64 oracle; values near the top of the fp32 range; the accuracy of long
+and of cancelling sums against fp64; and the sums' own error beside that of fp32 products.
 
-Bars: the parts add up to the value exactly and the dropped products are below 2^-23 of a
-product, so a Gram entry errs by less than the fp32 form's n rounding errors; with lambda n_u on the
-diagonal the systems here have condition numbers below 1e3, so 1e3 x 2^-23 = 1.2e-4 bounds a row,
-inside the parity bar of 1e-3; 2e-5 is asserted (measured: 3e-7 to 2e-6)."""
+Bars: the parts add up to the value exactly and the dropped products are below 2^-22 of a
+product; with lambda n_u on the diagonal the systems here have condition numbers below 1e3, so
+1e3 x 2^-22 = 2.4e-4 bounds a row, inside the parity bar of 1e-3; 2e-5 is asserted (measured: 3e-7
+to 2e-6)."""
 import os
 
 import numpy as np
@@ -90,3 +90,62 @@ def test_long_sums_keep_fp32_accuracy(length, mean):
     err = float(np.linalg.norm(x - xo) / np.linalg.norm(xo))
     print(f"[gpu] relative error {err:.2e}, bound {bound:.2e}")
     assert err <= bound
+
+
+def constants_with_large_parts(rng, shape):
+    """Values h + m + l whose middle part is near its largest, 2^-7 of the leading bit, and whose low part
+    is negative and near its largest, 2^-16: the products m l and l m, which the split form leaves
+    out, are near 2^-23 each and have one sign."""
+    h = 1.0 + rng.integers(0, 128, shape) / 128.0
+    m = (128 + 8 * rng.integers(0, 16, shape) + 7) * 2.0 ** -15
+    return (h + m - 0.9 * 2.0 ** -16).astype(np.float32)
+
+
+@pytest.mark.parametrize("f", [4, 6, 16, 36, 63, 100, 115, 128])
+@pytest.mark.parametrize("kind", ["random", "equal", "parts"])
+@pytest.mark.parametrize("form", ["buffer", "global"])
+def test_sums_err_no_more_than_fp32_products(f, kind, form):
+    """The error of b = sum r theta against fp64, by itself: with lambda n = 2^40 the Gram matrix is
+    below half a unit in the last place of the diagonal, every pivot is 2^40, and x = 2^-40 b without
+    another rounding.  It must not exceed that of fp32 products summed one after the other, each
+    entry an FMA (f a multiple of 16: four sums of every fourth entry, then their sum), neither at most
+    nor as a root mean square (a tenth more is allowed: both are estimates from some thousand sums), at
+    lengths on both sides of the shortest pieces' fp32 form (16 entries), where equal entries err
+    most, and of the 32-entry group; one product alone is rounded to nearest exactly."""
+    ctx = context(form, f)
+    rng = np.random.default_rng(f)
+    for length in (1, 2, 3, 8, 15, 16, 17, 20, 31, 32, 33, 64, 128):
+        m = max(64, 4096 // length)
+        shape = (m, length, f) if kind == "random" else (m, 1, f)
+        if kind == "parts":
+            theta = constants_with_large_parts(rng, shape)
+            vals = constants_with_large_parts(rng, shape[:2])
+        else:
+            theta = rng.uniform(0.5, 1.5, shape).astype(np.float32)
+            vals = rng.uniform(1.0, 5.0, shape[:2]).astype(np.float32)
+        theta = np.broadcast_to(theta, (m, length, f)).reshape(m * length, f).copy()
+        vals = np.broadcast_to(vals, (m, length)).reshape(-1).copy()
+        rowptr = np.arange(m + 1, dtype=np.int64) * length
+        log(f"gram split, sums of {length}, {kind}, f={f} {form}")
+        lam = 2.0 ** 40 / length
+        assert np.float32(np.float64(np.float32(lam)) * length) == np.float32(2.0 ** 40)
+        x = gpu_half_sweep(ctx, rowptr, np.arange(m * length, dtype=np.int32), vals, m, m * length, f,
+                           lam, theta)
+        got = x.astype(np.float64) * 2.0 ** 40
+        products = (vals[:, None].astype(np.float64) * theta).reshape(m, length, f)
+        slots = 4 if f % 16 == 0 else 1
+        chains = np.zeros((slots, m, f), np.float32)
+        for k in range(length):
+            at = k % slots
+            chains[at] = (chains[at].astype(np.float64) + products[:, k]).astype(np.float32)
+        chain = chains[0]
+        for other in chains[1:]:
+            chain = chain + other
+        b = products.sum(1)
+        err, ref = np.abs(got / b - 1.0), np.abs(chain / b - 1.0)
+        print(f"[gpu] max {err.max():.2e} chain {ref.max():.2e}; rms {np.sqrt((err ** 2).mean()):.2e} "
+              f"chain {np.sqrt((ref ** 2).mean()):.2e}")
+        if length == 1:
+            assert np.array_equal(got, chain.astype(np.float64))
+        assert err.max() <= 1.1 * ref.max()
+        assert (err ** 2).mean() <= 1.21 * (ref ** 2).mean()
