@@ -145,12 +145,14 @@ constexpr int64_t kStaticEntries = 2048;
 // Cost prefix P(u) = c_nnz rowptr[u] + c_row u, T = P(m).  C chunks: W large ones cover
 // T1 = T - T2 and C - W small ones the tail T2 = floor(T / kTailDiv) (T2 = 0 when C = W);
 // boundary b sits at s_b = floor(T1 b / W) for b <= W, T1 + floor(T2 (b - W) / (C - W)) beyond.
-// The first threads also reset the counters the persistent waves claim chunks from.
+// The first threads also reset the counters the persistent waves claim chunks from and the flag of
+// rows set aside (see kTinyX).
 __global__ void k_plan(const int64_t* __restrict__ rowptr, int64_t m, int W, int C, int64_t c_nnz,
                        int64_t c_row, int64_t q, int64_t* __restrict__ bounds,
-                       unsigned* __restrict__ chunk_ctr) {
+                       unsigned* __restrict__ chunk_ctr, unsigned* __restrict__ set_aside) {
     const int b = blockIdx.x * blockDim.x + threadIdx.x;
     if (b < kStripes && chunk_ctr) chunk_ctr[b * kStripeWords] = 0u;
+    if (b == 0 && set_aside) *set_aside = 0u;
     if (b > C) return;
     const int64_t T = c_nnz * rowptr[m] + c_row * m;
     const int64_t T2 = C > W ? T / kTailDiv : 0, T1 = T - T2;
@@ -1343,12 +1345,71 @@ __device__ __forceinline__ bool solve_core(f4 (&acc)[ntiles(NB)], int f, float l
     return ok;
 }
 
-// solve_core, then x_u (f floats, NaN if a pivot was not positive) to xrow.
+// ---- rows with a column of tiny values
+//
+// bf16 has fp32's exponents but no smaller subnormals than 2^-133, so a value below about 2^-110 loses
+// low bits with its parts.  That shows where all of a row's ratings, or a whole column of its gathered
+// factors, are that small (beside larger ones the loss is below 2^-24 of the column).  Then x_u, or
+// its entry for the column, is tiny too: at most the column's norm times that of the ratings over
+// lambda n_u (the ridge residual is no larger than the ratings), which is below kTinyX unless the
+// ratings exceed lambda 2^60-fold.  Rows with such an entry are set aside by k_herm_solve and summed
+// again with fp32 products, whose range is fp32's, in k_reduce_solve.  (With lambda = 0 such a column's
+// pivot underflows, and x_u is NaN either way.)  Rows with a zero in x_u are set aside as well.
+constexpr float kTinyX = 0x1p-40f;
+constexpr unsigned kSetAside = 0x7FA5A5A5u;   // a NaN that no solve writes: first value of a row set aside
+
+// The augmented Gram matrix of a row's entries [beg, end) with fp32 products, four entries a step;
+// the accumulators are rounded once per 16 entries.
+template <int NB>
+__device__ __forceinline__ void plain_row(f4 (&acc)[ntiles(NB)], const int32_t* __restrict__ colidx,
+                                          const float* __restrict__ vals,
+                                          const float* __restrict__ theta, int f, int64_t beg,
+                                          int64_t end, int lane) {
+    constexpr int kSteps = 4;
+    const int g = lane >> 4, c = lane & 15;
+#pragma unroll
+    for (int t = 0; t < ntiles(NB); ++t) acc[t] = f4{0.f, 0.f, 0.f, 0.f};
+    for (int64_t k = beg; k < end; k += 4 * kSteps) {
+        float x[kSteps][NB];
+#pragma unroll
+        for (int j = 0; j < kSteps; ++j) {
+            const int64_t e = k + 4 * j + g;
+            const bool valid = e < end;
+            const float* row = theta + (valid ? (size_t)(unsigned)colidx[e] * (size_t)f : 0);
+            const float r = valid ? vals[e] : 0.f;
+#pragma unroll
+            for (int I = 0; I < NB; ++I) {
+                const int v = 16 * I + c;
+                x[j][I] = valid && v < f ? row[v] : (v == f ? r : 0.f);
+            }
+        }
+#pragma unroll
+        for (int I = 0; I < NB; ++I)
+#pragma unroll
+            for (int J = I; J < NB; ++J) {
+                f4 t = f4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+                for (int j = 0; j < kSteps; ++j)
+                    t = __builtin_amdgcn_mfma_f32_16x16x4f32(x[j][I], x[j][J], t, 0, 0, 0);
+                acc[tu(NB, I, J)] += t;
+            }
+    }
+}
+
+// solve_core, then x_u (f floats, NaN if a pivot was not positive) to xrow.  tiny: whether an entry of
+// x_u is below kTinyX.
 template <int NB>
 __device__ __forceinline__ bool solve_row(f4 (&acc)[ntiles(NB)], int f, float lam_n,
-                                          SolveLds<NB>& S, float* __restrict__ xrow, int lane) {
+                                          SolveLds<NB>& S, float* __restrict__ xrow, int lane,
+                                          bool& tiny) {
     const bool ok = solve_core<NB>(acc, f, lam_n, S, lane);
-    for (int j = lane; j < f; j += kWave) xrow[j] = ok ? S.x[j] : __builtin_nanf("");
+    bool below = false;
+    for (int j = lane; j < f; j += kWave) {
+        const float x = ok ? S.x[j] : __builtin_nanf("");
+        below |= __builtin_fabsf(x) < kTinyX;
+        xrow[j] = x;
+    }
+    tiny = __ballot(below) != 0;
     return ok;
 }
 
@@ -1394,7 +1455,8 @@ void k_herm_solve(
     const float* __restrict__ vals, const float* __restrict__ theta, int64_t m, int64_t n,
     int f, float lambda, int C, const int64_t* __restrict__ bounds, float* __restrict__ x_out,
     float* __restrict__ slots, float* __restrict__ wave_slots, int part_mask, int64_t c_row,
-    unsigned long long* __restrict__ nonspd, unsigned* __restrict__ chunk_ctr) {
+    unsigned long long* __restrict__ nonspd, unsigned* __restrict__ chunk_ctr,
+    unsigned* __restrict__ set_aside) {
     // Where a piece may be longer than a part, both instantiations (with and without parts) are
     // launched, and the one that does not match this call returns at once.  A piece lies within a chunk and within a row: a chunk holds at
     // most ceil(T1 / W) cost units (c_nnz per entry) plus the snapping of its two cut offsets,
@@ -1499,7 +1561,12 @@ void k_herm_solve(
             if (cur.whole) {
                 const int64_t nu = cur.end - cur.beg;
                 const float lam_n = (float)((double)lambda * (double)nu);
-                if (!solve_row<NB>(acc, f, lam_n, lds, x_out + (size_t)cur.u * f, lane)) ++bad;
+                bool tiny;
+                if (!solve_row<NB>(acc, f, lam_n, lds, x_out + (size_t)cur.u * f, lane, tiny)) ++bad;
+                if (__builtin_expect(tiny, 0)) {   // (every lane stores the same value)
+                    x_out[(size_t)cur.u * f] = __builtin_bit_cast(float, kSetAside);
+                    *set_aside = 1u;
+                }
             } else {
                 const int which = (cur.u == u0) ? 0 : 1;
                 store_slot<NB>(acc, slots + (size_t)(2 * c + which) * slot_floats(NB), lane);
@@ -1653,8 +1720,11 @@ __global__ __launch_bounds__(kWave) void k_reduce_groups(
 
 // Pass 2: the first boundary that cuts a row sums its pieces (or its group sums) and solves it.
 template <int NB>
-__device__ __forceinline__ void reduce_row(const int64_t* __restrict__ rowptr, int64_t m, int C,
-                                           int f, float lambda, const int64_t* __restrict__ bounds,
+__device__ __forceinline__ void reduce_row(const int64_t* __restrict__ rowptr,
+                                           const int32_t* __restrict__ colidx,
+                                           const float* __restrict__ vals,
+                                           const float* __restrict__ theta, int64_t m, int C, int f,
+                                           float lambda, const int64_t* __restrict__ bounds,
                                            float* __restrict__ x_out,
                                            const float* __restrict__ slots, unsigned& bad,
                                            SolveLds<NB>& lds, int b, int lane) {
@@ -1679,14 +1749,45 @@ __device__ __forceinline__ void reduce_row(const int64_t* __restrict__ rowptr, i
             add_slot<NB>(acc, slots + (size_t)(2 * g) * slot_floats(NB), lane);
     }
     const float lam_n = (float)((double)lambda * (double)nu);
-    if (!solve_row<NB>(acc, f, lam_n, lds, x_out + (size_t)u * f, lane)) ++bad;
+    for (bool tiny = false, again = false;; again = true) {
+        if (again) plain_row<NB>(acc, colidx, vals, theta, f, rowptr[u], rowptr[u + 1], lane);
+        if (!solve_row<NB>(acc, f, lam_n, lds, x_out + (size_t)u * f, lane, tiny)) ++bad;
+        if (again || !tiny) break;
+    }
+}
+
+// The rows that k_herm_solve has set aside: a wave looks at 64 rows at once.
+template <int NB>
+__device__ __forceinline__ void solve_set_aside(const int64_t* __restrict__ rowptr,
+                                                const int32_t* __restrict__ colidx,
+                                                const float* __restrict__ vals,
+                                                const float* __restrict__ theta, int64_t m, int f,
+                                                float lambda, float* __restrict__ x_out,
+                                                unsigned& bad, SolveLds<NB>& lds, int lane) {
+    for (int64_t u0 = (int64_t)blockIdx.x * kWave; u0 < m; u0 += (int64_t)gridDim.x * kWave) {
+        const int64_t u = u0 + lane;
+        uint64_t todo = __ballot(
+            u < m && reinterpret_cast<const unsigned*>(x_out)[(size_t)u * f] == kSetAside);
+        while (todo) {
+            const int64_t v = u0 + __builtin_ctzll(todo);
+            todo &= todo - 1;
+            const int64_t beg = rowptr[v], end = rowptr[v + 1];
+            f4 acc[ntiles(NB)];
+            plain_row<NB>(acc, colidx, vals, theta, f, beg, end, lane);
+            const float lam_n = (float)((double)lambda * (double)(end - beg));
+            bool tiny;
+            if (!solve_row<NB>(acc, f, lam_n, lds, x_out + (size_t)v * f, lane, tiny)) ++bad;
+        }
+    }
 }
 
 template <int NB>
 __global__ __launch_bounds__(kWave) void k_reduce_solve(
-    const int64_t* __restrict__ rowptr, int64_t m, int C, int f, float lambda,
-    const int64_t* __restrict__ bounds, float* __restrict__ x_out,
-    const float* __restrict__ slots, unsigned long long* __restrict__ nonspd) {
+    const int64_t* __restrict__ rowptr, const int32_t* __restrict__ colidx,
+    const float* __restrict__ vals, const float* __restrict__ theta, int64_t m, int C, int f,
+    float lambda, const int64_t* __restrict__ bounds, float* __restrict__ x_out,
+    const float* __restrict__ slots, unsigned long long* __restrict__ nonspd,
+    const unsigned* __restrict__ set_aside) {
     __shared__ __attribute__((aligned(16))) SolveLds<NB> lds;
     const int lane = threadIdx.x;
     unsigned bad = 0;   // non-SPD rows of this wave, added once after the loop
@@ -1696,8 +1797,11 @@ __global__ __launch_bounds__(kWave) void k_reduce_solve(
                  cuts_row(rowptr, m, bounds, b - 1));
     };
     for_boundaries(C, lane, first_cut, [&](int b) {
-        reduce_row<NB>(rowptr, m, C, f, lambda, bounds, x_out, slots, bad, lds, b, lane);
+        reduce_row<NB>(rowptr, colidx, vals, theta, m, C, f, lambda, bounds, x_out, slots, bad,
+                       lds, b, lane);
     });
+    if (*set_aside)
+        solve_set_aside<NB>(rowptr, colidx, vals, theta, m, f, lambda, x_out, bad, lds, lane);
     bad = __builtin_amdgcn_readfirstlane(bad);
     if (bad) atomicAdd(nonspd, lane == 0 ? (unsigned long long)bad : 0ull);
 }
@@ -2488,7 +2592,8 @@ Layout make_layout(const int (*waves)[kLastForms], int nb_max, int cus) {
     }
     Layout L;
     size_t off = 0;
-    // non-SPD counter at 0, RMSE chunk counter at 128, the half-sweep's chunk counters from 256 on
+    // non-SPD counter at 0, RMSE chunk counter at 128, flag of rows set aside at 192, the half-sweep's
+    // chunk counters from 256 on
     L.status = off; off = align256(off + 256 + sizeof(unsigned) * kStripes * kStripeWords);
     L.bounds = off; off = align256(off + sizeof(int64_t) * 2 * (size_t)(c_cap + 1));
     L.rmse = off;   off = align256(off + sizeof(double) * (size_t)cus * kRmseWavesPerCU);
@@ -2750,6 +2855,7 @@ struct HermArgs {
     int64_t c_row;
     unsigned long long* nonspd;
     unsigned* chunk_ctr;
+    unsigned* set_aside;
 };
 
 // A row has at most n entries (its columns are distinct), so with n no longer than a part no piece
@@ -2760,12 +2866,12 @@ void launch_herm(int W, hipStream_t st, const HermArgs& a) {
     hipLaunchKernelGGL((k_herm_solve<NB, BUF, LAST, false>), dim3(W), dim3(kWave), 0, st,
                        a.rowptr, a.colidx, a.vals, a.theta, a.m, a.n, a.f, a.lambda, a.C,
                        a.bounds, a.x, a.slots, a.wslots, a.part_mask, a.c_row, a.nonspd,
-                       a.chunk_ctr);
+                       a.chunk_ctr, a.set_aside);
     if (a.n <= (int64_t)kGroupEntries * (a.part_mask + 1)) return;
     hipLaunchKernelGGL((k_herm_solve<NB, BUF, LAST, true>), dim3(W), dim3(kWave), 0, st,
                        a.rowptr, a.colidx, a.vals, a.theta, a.m, a.n, a.f, a.lambda, a.C,
                        a.bounds, a.x, a.slots, a.wslots, a.part_mask, a.c_row, a.nonspd,
-                       a.chunk_ctr);
+                       a.chunk_ctr, a.set_aside);
 }
 
 // fn with the form of the last block column as a constant.
@@ -2790,15 +2896,17 @@ void launch_sweep(als_ctx* ctx, const int64_t* rowptr, const int32_t* colidx, co
     const int part_mask = ctx->part_groups - 1;
     auto* nonspd = (unsigned long long*)(ctx->ws + ctx->lay.status);
     auto* chunk_ctr = (unsigned*)(ctx->ws + ctx->lay.status + 256);
+    auto* set_aside = (unsigned*)(ctx->ws + ctx->lay.status + 192);
     const int C = chunks_of(W);
     hipEvent_t* ev = nullptr;
     if (ctx->prof_ev && ctx->prof_count < ctx->prof_cap) ev = ctx->prof_ev + 4 * ctx->prof_count++;
     if (ev) (void)hipEventRecord(ev[0], st);
     hipLaunchKernelGGL(k_plan, dim3((C + 1 + 63) / 64), dim3(64), 0, st, rowptr, m, W, C,
-                       (int64_t)kCostPerEntry, row_cost(f), (int64_t)kSnap, bounds, chunk_ctr);
+                       (int64_t)kCostPerEntry, row_cost(f), (int64_t)kSnap, bounds, chunk_ctr,
+                       set_aside);
     if (ev) (void)hipEventRecord(ev[1], st);
     const HermArgs a{rowptr, colidx, vals, theta, m, n, f, lambda, C, bounds, x, slots, wslots,
-                     part_mask, row_cost(f), nonspd, chunk_ctr};
+                     part_mask, row_cost(f), nonspd, chunk_ctr, set_aside};
     const bool buf = !ctx->global_gather &&
                      (uint64_t)n * (uint64_t)f * sizeof(float) <= kBufferGatherMax;
     if (ctx->staged_gather) {   // f % 4 == 0 and theta below 2 GiB (checked by the caller)
@@ -2814,8 +2922,8 @@ void launch_sweep(als_ctx* ctx, const int64_t* rowptr, const int32_t* colidx, co
         const int grid = C - 1 < kReduceWaves ? C - 1 : kReduceWaves;
         hipLaunchKernelGGL(k_reduce_groups<NB>, dim3(grid), dim3(kWave), 0, st, rowptr, m, C,
                            bounds, slots);
-        hipLaunchKernelGGL(k_reduce_solve<NB>, dim3(grid), dim3(kWave), 0, st, rowptr, m, C, f,
-                           lambda, bounds, x, slots, nonspd);
+        hipLaunchKernelGGL(k_reduce_solve<NB>, dim3(grid), dim3(kWave), 0, st, rowptr, colidx, vals,
+                           theta, m, C, f, lambda, bounds, x, slots, nonspd, set_aside);
     }
     if (ev) (void)hipEventRecord(ev[3], st);
 }
@@ -3262,7 +3370,7 @@ int als_plan(als_ctx* ctx, const int64_t* rowptr, int64_t m, int32_t f, int64_t*
     if (!guard.ok) return ALS_ERR_DEVICE;
     hipLaunchKernelGGL(k_plan, dim3((C + 1 + 63) / 64), dim3(64), 0, (hipStream_t)stream, rowptr,
                        m, W, C, (int64_t)kCostPerEntry, row_cost(f), (int64_t)kSnap, bounds_out,
-                       nullptr);
+                       nullptr, nullptr);
     hipError_t e = hipGetLastError();
     return e == hipSuccess ? ALS_OK : fail_hip(ctx, e);
 }

@@ -149,3 +149,54 @@ def test_sums_err_no_more_than_fp32_products(f, kind, form):
             assert np.array_equal(got, chain.astype(np.float64))
         assert err.max() <= 1.1 * ref.max()
         assert (err ** 2).mean() <= 1.21 * (ref ** 2).mean()
+
+
+@pytest.mark.parametrize("f", [6, 16, 20, 63, 100, 115, 128])
+@pytest.mark.parametrize("exponent", [-105, -115, -122])
+@pytest.mark.parametrize("what", ["ratings", "theta", "column", "zeros"])
+def test_tiny_values_keep_their_bits(f, exponent, what):
+    """bf16's smallest numbers are fp32's, but not its subnormals, so the parts of values below about
+    2^-110 lose bits; rows whose ratings, or a whole column of whose factors, are that small are summed
+    with fp32 products.  Whole rows and rows cut between chunks (30,000 entries), scaled by a power of
+    two: x_u (of "column": its entry for the column) agrees with fp64 as it does unscaled (twice that
+    error and 2e-5, plus what results that small lose to fp32's own subnormals)."""
+    rng = np.random.default_rng(f - exponent)
+    n = 40_000
+    rowptr, colidx = rows(rng, n, [3, 17, 40, 64, 200, 1_500, 30_000, 33, 30_000, 16])
+    m = len(rowptr) - 1
+    vals = rng.uniform(1.0, 5.0, size=int(rowptr[-1])).astype(np.float32)
+    theta = (rng.normal(size=(n, f)) * f ** -0.5 + 0.05).astype(np.float32)
+    plain = vals.copy(), theta.copy()
+    scale = np.float32(2.0 ** exponent)
+    if what == "ratings":
+        vals *= scale
+    elif what == "theta":
+        theta *= scale
+    elif what == "column":
+        theta[:, f // 2] *= scale
+    else:   # a column and a row's ratings of zeros
+        theta[:, f // 2] = 0.0
+        vals[rowptr[3]:rowptr[4]] = 0.0
+    log(f"gram split, tiny {what}, 2^{exponent}, f={f}")
+
+    def both(vals, theta):
+        xo, _ = oracle.get().half_sweep(rowptr, colidx, vals, m, n, f, 0.05, theta.astype(np.float64))
+        return [gpu_half_sweep(context(form, f), rowptr, colidx, vals, m, n, f, 0.05, theta)
+                for form in ("buffer", "global")], xo
+
+    bar = row_rel_err(*(a if i else a[0] for i, a in enumerate(both(*plain)))).max() * 2 + 2e-5
+    results, xo = both(vals, theta)
+    for x in results:
+        assert np.isfinite(x).all()
+        if what == "column":
+            # its other entries as ever; the entry is a difference of sums of its size, so a cancellation
+            # down to a tenth is allowed for
+            assert row_rel_err(np.delete(x, f // 2, 1), np.delete(xo, f // 2, 1)).max() <= bar
+            got, ref = x[:, f // 2].astype(np.float64), xo[:, f // 2]
+            assert np.abs(got - ref).max() <= 10 * bar * np.abs(ref).max() + f * 2.0 ** -146
+        elif what == "zeros":
+            assert np.all(x[:, f // 2] == 0.0) and np.all(x[3] == 0.0)
+            assert row_rel_err(np.delete(x, 3, 0), np.delete(xo, 3, 0)).max() <= bar
+        else:
+            err = np.abs(x.astype(np.float64) - xo).max(axis=1)
+            assert np.all(err <= bar * np.abs(xo).max(axis=1) + f * 2.0 ** -146)
