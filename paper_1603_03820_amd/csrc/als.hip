@@ -901,6 +901,15 @@ struct GramBody {
     }
 };
 
+// The lane, computed on the spot: an address made from it is not kept in a register across the loop, or
+// spilled and loaded again, which waits for every gather in flight (the parts form at f = 100 did so
+// once per 64 entries).
+__device__ __forceinline__ int fresh_lane() {
+    unsigned zero = 0;
+    asm volatile("" : "+s"(zero));
+    return (int)__builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, zero));
+}
+
 // The first batch of a piece into ring slot `slot`, and the gathers of its first group.
 template <class G>
 __device__ __forceinline__ void start_piece(const G& gat, const typename G::Entry& first,
@@ -929,8 +938,7 @@ __device__ __forceinline__ void group_loop(const G& gat, const int32_t* __restri
     const int ngroups = (total + kGroupEntries - 1) / kGroupEntries;
     if constexpr (Body::kPlain) {
         if (total <= kPlainEntries) {
-            int l = lane;   // (opaque: addresses from it are not kept in registers across rows)
-            asm volatile("" : "+v"(l));
+            const int l = fresh_lane();
             const typename G::Entry* cur = ring + slot * kGramBatch;
             if (total <= kPlainEntries / 2) body.template plain<kPlainEntries / 8>(raw, cur, l >> 4);
             else body.template plain<kPlainEntries / 4>(raw, cur, l >> 4);
@@ -955,7 +963,7 @@ __device__ __forceinline__ void group_loop(const G& gat, const int32_t* __restri
         if (last ? more : odd) {
             // (by members: a choice between the objects is one between addresses, and keeps both in
             // private memory)
-            ring[other * kGramBatch + lane] =
+            ring[other * kGramBatch + fresh_lane()] =
                 typename G::Entry{last ? next_first.e : nq.e, last ? next_first.r : nq.r};
             __syncthreads();
             next = ring + other * kGramBatch;
