@@ -136,7 +136,8 @@ __device__ __forceinline__ float row_sum16_t(f4 v) {
 //   - a longer one, whose waves finish at different times, claims from kStripes counters on lines
 //     of their own: stripe s holds chunks s, s + kStripes, ... in order, for the waves of blocks
 //     b with b / 8 = s (mod kStripes), which lie on all XCDs (block b runs on XCD b mod 8).  A
-//     stripe's 128 or more waves even it out among themselves, so none goes on to another stripe
+//     stripe's 64 or more waves (W = 1,024 at f = 128) even it out among themselves, so none goes on to
+//     another stripe
 //     (looking at the other counters at the end made the kernel twice as long).
 constexpr int kStripes = 16;                    // a power of two
 constexpr int kStripeWords = 64;                // 256 bytes apart
@@ -600,12 +601,20 @@ constexpr int gram_registers(int nb, int last) {
     return 4 * gram_tiles(nb, last) + 12 * (last == kLastTiles ? nb : nb - 1) +
            (last == kLastPacked ? 4 : 0) + (last == kLastRating ? nb - 1 : 0);
 }
+// f = 113 to 127 take fp32 products throughout, in half groups of 16 entries: with the parts beside 144
+// accumulator registers only one wave per SIMD fits, and nothing runs beside its solve.  2M ratings of
+// 400,000 users at f = 113 and 120: 8.65 and 8.47 ms with parts, 6.81 and 6.54 so; 20M of 200,000
+// users 6.05 and 6.03, 6.18 and 5.94.  (The products of every four entries straight into the
+// accumulators: 6.62, 6.45, 5.88 and 5.73, but an error against fp64 of 2.7e-6 instead of 1.5e-6 on
+// the longer rows.)  f = 112 fits two waves with its parts: 4.1 ms, with one wave 5.7.
+constexpr bool gram_fp32(int nb, int last) { return nb == 8 && last != kLastRating; }
 // The least waves per SIMD that the compiler is held to: two where accumulators and parts leave 50
 // registers of 256 for the rest, and what f = 16, 32 and 48 take without spilling (the 64-bit parts
 // form, whose waves bound the others', would take 102 and 130 registers at f = 16 and 32 and lose one
 // of five and of four waves: 361 against 327 us on 20M ratings of 200,000 users at f = 16, 659 against
 // 573 at f = 32).
 constexpr int gram_waves(int nb, int last) {
+    if (gram_fp32(nb, last)) return 2;
     if (nb <= 4 && last == kLastRating) return 7 - nb;
     return gram_registers(nb, last) <= 206 ? 2 : 1;
 }
@@ -810,7 +819,8 @@ __device__ __forceinline__ void fold_rating(f4 (&acc)[ntiles(NB)], const float (
 
 template <int NB, int LAST, class G, bool PARTS>
 struct GramBody {
-    static constexpr bool kParts = PARTS, kPlain = true;
+    static constexpr bool kFp32 = gram_fp32(NB, LAST);
+    static constexpr bool kParts = PARTS, kPlain = !kFp32;
     static constexpr int kTop = LAST == kLastRating ? NB - 2 : NB - 1;   // last column of products
     int part_mask;        // groups per part - 1 (a power of two - 1)
     const G& gat;
@@ -820,6 +830,7 @@ struct GramBody {
     void* scratch;        // LDS for fold_packed and fold_rating
     float* wslot;         // the wave's slot
     int lane;
+    const typename G::Entry* cur = nullptr;   // kFp32: the group's entries
     Cut cut = kUpperHalf; // kNothing: the piece's products are in acc already (plain)
     float b[NB > 1 ? NB - 1 : 1];   // kLastRating: the rating column's sums
     Parts<NB, LAST> a;
@@ -860,6 +871,10 @@ struct GramBody {
     }
     // the group's operands from its gathered values and its ratings (in the ring)
     __device__ __forceinline__ void take(const Raw<G>& raw, const typename G::Entry* ring) {
+        if constexpr (kFp32) {
+            cur = ring;
+            return;
+        }
         const int g = lane >> 4;
 #pragma unroll
         for (int p = 0; p < kGroupSteps / 2; ++p) {
@@ -884,6 +899,33 @@ struct GramBody {
         }
     }
     __device__ __forceinline__ void run(const typename G::Entry* next, Raw<G>& raw) {
+        if constexpr (kFp32) {
+            const int g = lane >> 4;
+            constexpr int kHalf = kGroupSteps / 2;
+#pragma unroll
+            for (int j0 = 0; j0 < kGroupSteps; j0 += kHalf) {
+                float x[kHalf][G::kBlocks];
+#pragma unroll
+                for (int j = 0; j < kHalf; ++j) {
+                    gat.operands(raw.b[j0 + j], cur[4 * (j0 + j) + g].r, x[j]);
+                    if constexpr (LAST == kLastPacked) x[j][NB - 1] = third == 0 ? x[j][NB - 1] : 0.f;
+                }
+#pragma unroll
+                for (int I = 0; I <= kTop; ++I)
+#pragma unroll
+                    for (int J = I; J <= kTop; ++J) {
+                        f4 t = f4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+                        for (int j = 0; j < kHalf; ++j)
+                            t = __builtin_amdgcn_mfma_f32_16x16x4f32(x[j][I], x[j][J], t, 0, 0, 0);
+                        acc[tu(NB, I, J)] += t;
+                    }
+                __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                for (int j = j0; j < j0 + kHalf; ++j) gat.issue(next[4 * j + g].e, raw.b[j]);
+            }
+            return;
+        }
         issue_steps<0, steps_before<NB, LAST>(kTop)>(gat, next, lane >> 4, raw);
         tile_columns<NB, LAST, kTop>(a, acc, gat, next, lane >> 4, raw);
     }
