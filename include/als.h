@@ -116,7 +116,8 @@ int als_rmse(als_ctx* ctx, const int64_t* rowptr, const int32_t* colidx, const f
 
 /* Width of later als_rmse calls on this context: at most `waves_per_simd` resident waves per
    SIMD (1..8), or as many as fit (0, the default).  The entries are always cut into the same
-   fixed chunks, claimed by the running waves in order, and summed per chunk in a fixed order,
+   fixed chunks, a chunk to a wave or claimed in order by fewer waves, and summed per chunk in a
+   fixed order,
    so the result does not depend on the width.  A narrow RMSE can run beside a half-sweep of
    another context (its own workspace) on another stream; where the half-sweep's waves hold all
    of a SIMD's registers (f from about 80 on), its waves take the place of some of them.  ALS_ERR_INVALID_ARG outside 0..8. */
@@ -132,8 +133,8 @@ int als_rmse_waves(als_ctx* ctx, int32_t waves_per_simd);
  * one copy per device, held until the process ends.  The call allocates nothing: no hipMalloc,
  * no hipFree, no allocating library routine.  Set-up (the device query and the array's device
  * address) runs once per device, in als_init on that device or else in the first call; later
- * calls only check arguments and queue three kernels on `stream` (the counter is cleared by a
- * kernel, not a memset).  Every call on one device shares that device's array: calls that
+ * calls only check arguments and queue two kernels on `stream`, with a third before them that
+ * clears the counter (not a memset) where fewer waves fit than there are chunks.  Every call on one device shares that device's array: calls that
  * overlap in time on one device -- on different streams or from different host threads --
  * race and give undefined results; the caller orders them.  Arguments, layout and errors as
  * als_rmse; ALS_ERR_DEVICE if `device` is invalid or not a gfx950 device.
@@ -155,8 +156,10 @@ int als_status(als_ctx* ctx, void* stream, int64_t* nonspd_rows);
  * T1 + floor(T2 (b - W) / (C - W)) for b > W: in row u_b, the largest u with P(u) <= s_b, at
  * entry offset k_b = ceil((s_b - P(u_b) - c_row) / c_nnz) clamped to [0, n_u], rounded to the
  * nearest multiple of q and, if not 0, moved to n_u when fewer than q/2 entries would remain.
- * Chunk c takes the entries from (u_c, k_c) up to (u_{c+1}, k_{c+1}); the waves claim chunks in
- * order from a counter, so the large chunks go first and the small ones even out the finish.  A
+ * Chunk c takes the entries from (u_c, k_c) up to (u_{c+1}, k_{c+1}).  In a short sweep wave w runs
+ * large chunk w and an equal share of the small ones; in a longer one the waves claim chunks in
+ * order from 16 counters, each for every 16th chunk, so the large chunks go first and the small
+ * ones even out the finish.  A
  * row cut by a boundary is finished by a second pass that sums its pieces in chunk order, so the
  * result does not depend on which wave ran which chunk.
  *   bounds_out : DEVICE int64[2 (C+1)], (u_b, k_b) pairs; capacity in pairs (>= C + 1, else

@@ -24,22 +24,13 @@ def _bench(config, *extra):
 @pytest.mark.gpu
 @pytest.mark.parametrize("config", ["tiny", "movie"])
 def test_overlapped_step_matches_serial(config):
-    ov = _bench(config)
-    se = _bench(config, "--serial-rmse")
-    assert ov["nonspd_rows"] == 0 and se["nonspd_rows"] == 0
-    assert ov["train_rmse"] == se["train_rmse"]
-    assert 0.0 < ov["train_rmse"] < 10.0
-
-
-@pytest.mark.gpu
-@pytest.mark.parametrize("config", ["tiny", "movie"])
-def test_overlap_option_matches_serial(config):
     """--overlap-rmse, the step described above, against the default order of the calls."""
     ov = _bench(config, "--overlap-rmse")
     se = _bench(config)
     assert "second stream" in ov["config"]["step"] and "second stream" not in se["config"]["step"]
     assert ov["nonspd_rows"] == 0 and se["nonspd_rows"] == 0
     assert ov["train_rmse"] == se["train_rmse"]
+    assert 0.0 < ov["train_rmse"] < 10.0
 
 
 @pytest.mark.gpu

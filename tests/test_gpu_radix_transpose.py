@@ -108,19 +108,24 @@ def test_agrees_with_the_oracle(oracle_lib):
         assert np.array_equal(a.cpu().numpy(), np.asarray(b))
 
 
-@pytest.mark.parametrize("n,nnz", [(3_000, 2_000_000), (80_000, 2_000_000)])
-def test_both_sides_of_the_capacity(monkeypatch, n, nnz):
-    """The smallest workspace (f_max = 1, one wave per CU) holds a known number of entries; more of
-    them take the counting form."""
+@pytest.mark.parametrize("n", [3_000, 80_000])
+@pytest.mark.parametrize("over", [0, 1, 100_000])
+def test_both_sides_of_the_capacity(monkeypatch, n, over):
+    """As many entries as the smallest workspace (f_max = 1, one wave per CU) holds, sorted in two and
+    three passes in arrays that fill it, and more, which take the counting form."""
     from paper_1603_03820_amd import als
     monkeypatch.setenv("ALS_WAVES_PER_CU", "1")
     ctx = als.Context(0, 1)
+    m, nnz = 6_000, capacity(ctx, n) + over
     rng = np.random.default_rng(n)
-    for count in (nnz, nnz // 8):
-        rowptr, colidx, vals = matrix(rng, 6_000, n, count, "skewed")
-        log(f"radix transpose beside the counting form n={n} nnz={int(rowptr[-1])} "
-            f"workspace {ctx.workspace.numel()}")
-        check(ctx, 6_000, n, rowptr, colidx, vals)
+    counts = np.full(m, nnz // m) + (np.arange(m) < nnz % m)
+    assert 100_000 < nnz <= m * n and counts.max() <= n
+    rowptr = np.concatenate([[0], np.cumsum(counts)]).astype(np.int64)
+    place = rng.permutation(n).astype(np.int32)
+    start = (rng.random(m) ** 3 * n).astype(np.int64)
+    at = np.repeat(start - rowptr[:-1], counts) + np.arange(nnz)
+    log(f"radix transpose at its capacity n={n} nnz={nnz} workspace {ctx.workspace.numel()}")
+    check(ctx, m, n, rowptr, place[at % n], rng.standard_normal(nnz).astype(np.float32))
 
 
 @pytest.mark.parametrize("n", [200, 2_900])
