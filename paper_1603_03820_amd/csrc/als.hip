@@ -1612,7 +1612,11 @@ void k_herm_solve(
                 const int64_t nu = cur.end - cur.beg;
                 const float lam_n = (float)((double)lambda * (double)nu);
                 bool tiny;
-                if (!solve_row<NB>(acc, f, lam_n, lds, x_out + (size_t)cur.u * f, lane, tiny)) ++bad;
+                // (its LDS addresses are made per row in the parts form, which has no registers to keep
+                // them in; spilled, they were 51 loads a row: music item side 27.5 -> 32 ms)
+                if (!solve_row<NB>(acc, f, lam_n, lds, x_out + (size_t)cur.u * f,
+                                   PARTS ? fresh_lane() : lane, tiny))
+                    ++bad;
                 if (__builtin_expect(tiny, 0)) {   // (every lane stores the same value)
                     x_out[(size_t)cur.u * f] = __builtin_bit_cast(float, kSetAside);
                     *set_aside = 1u;
