@@ -130,7 +130,7 @@ __device__ __forceinline__ float row_sum16_t(f4 v) {
 // performed one after the other, about 11.5 ns each on this part: with one counter the 9W
 // successful and W failing claims of a half-sweep took 0.47 ms at W = 4,096 (f = 16 and 40: all of
 // the time of a call on 50,000 or 1M ratings), and the waves' first claims alone 25-47 us.  So
-//   - a short sweep (at most kStaticEntries entry equivalents of cost per wave) claims nothing: wave
+//   - a short sweep (at most static_entries entry equivalents of cost per wave) claims nothing: wave
 //     w runs large chunk w and the eight small chunks W + 8w .. W + 8w + 7, an equal share of the
 //     cost;
 //   - a longer one, whose waves finish at different times, claims from kStripes counters on lines
@@ -141,7 +141,11 @@ __device__ __forceinline__ float row_sum16_t(f4 v) {
 //     (looking at the other counters at the end made the kernel twice as long).
 constexpr int kStripes = 16;                    // a power of two
 constexpr int kStripeWords = 64;                // 256 bytes apart
-constexpr int64_t kStaticEntries = 2048;
+// Fixed shares against claims, 10M, 6M and 4M cost entries at f = 16, 40 and 100 (2,048 a wave): 134
+// against 157, 212 against 223, 561 against 522 us; a quarter of that: 58, 88, 211 against 91, 110,
+// 212; four times: 445, 722, 1,921 against 438, 686, 1,774.
+constexpr int64_t kStaticEntries = 2048;        // up to 3 column blocks
+constexpr int64_t static_entries(int nb) { return nb <= 3 ? kStaticEntries : kStaticEntries / 4; }
 
 // Cost prefix P(u) = c_nnz rowptr[u] + c_row u, T = P(m).  C chunks: W large ones cover
 // T1 = T - T2 and C - W small ones the tail T2 = floor(T / kTailDiv) (T2 = 0 when C = W);
@@ -1538,7 +1542,7 @@ void k_herm_solve(
     unsigned bad = 0;
     const int W = (int)gridDim.x, self = (int)blockIdx.x;
     const bool fixed = kCostPerEntry * rowptr[m] + c_row * m <=
-                       kStaticEntries * kCostPerEntry * (int64_t)W;
+                       static_entries(NB) * kCostPerEntry * (int64_t)W;
     bool first = true;
     const int stripes = W >= 8 * kStripes ? kStripes : 1;   // each with waves of its own
     const int stripe = (self >> 3) & (stripes - 1);
