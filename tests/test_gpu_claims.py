@@ -11,21 +11,23 @@ from tests.gpu_util import gpu_half_sweep, log, row_rel_err
 
 pytestmark = pytest.mark.gpu
 
-STATIC_ENTRIES = 2048   # kStaticEntries: entry equivalents per wave up to which shares are fixed
+# rank -> entry equivalents per wave up to which shares are fixed (fewer from four column blocks on)
+STATIC_ENTRIES = {8: 2048, 47: 2048, 50: 512}
 
 
+@pytest.mark.parametrize("f", sorted(STATIC_ENTRIES))
 @pytest.mark.parametrize("over", [0, 1])
 @pytest.mark.parametrize("waves_per_cu", [None, 1])
-def test_fixed_shares_and_claims(monkeypatch, oracle_lib, over, waves_per_cu):
+def test_fixed_shares_and_claims(monkeypatch, oracle_lib, f, over, waves_per_cu):
     from paper_1603_03820_amd import als
     if waves_per_cu:
         monkeypatch.setenv("ALS_WAVES_PER_CU", str(waves_per_cu))
-    f, n, per_row = 8, 300, 40
+    n, per_row = 300, 40
     ctx = als.Context(0, f)
     dummy = torch.zeros(2, dtype=torch.int64, device=ctx.device)
     _, (chunks, c_nnz, c_row, _, waves, _) = als.als_plan(ctx, dummy, 1, f)
     # the largest m whose cost is within the limit, or one row more
-    m = STATIC_ENTRIES * c_nnz * waves // (c_nnz * per_row + c_row) + over
+    m = STATIC_ENTRIES[f] * c_nnz * waves // (c_nnz * per_row + c_row) + over
     log(f"claims: W={waves} C={chunks} m={m} over={over}")
     rng = np.random.default_rng(7)
     rowptr = np.arange(m + 1, dtype=np.int64) * per_row
